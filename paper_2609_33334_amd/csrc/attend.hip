@@ -2,8 +2,9 @@
 // evicted cache (Sec. 3 Eq. 1; the eviction-mass equation of App. "Why deferral can
 // recover FullKV"; App. "Attention-matching loss").
 //
-// One workgroup per (query row of a sequence, KV head) handles the G query heads of
-// the group, so each cache row is read once for all of them.  The attended rows are
+// bf16 caches take the matrix-core kernel further down.  For fp32 caches one workgroup per
+// (query row of a sequence, KV head) handles the G query heads of the group, so each cache
+// row is read once for all of them.  The attended rows are
 // contiguous, [0, n_kept + visible tail), and go in chunks of 256 keys:
 //   - thread t computes the G logits of key c0 + t (its K row in 16-byte loads, the
 //     query rows broadcast from LDS), in the log2 domain;
@@ -40,33 +41,15 @@ struct AttArgs {
   float* beta;                        // MASS: [batch][H_kv] mean rho
   float* l_match;                     // MASS: [batch][H_kv] mean -log(1 - rho)
   int batch, n_kv_heads, G, n_q, q_from_end, n_select, n_tail, n_out;
+  int row_blocks;                     // matrix-core path: row blocks per (query head, sequence)
   float scale_log2;                   // log2(e) / sqrt(d)
 };
 
-__device__ __forceinline__ float elem_f32(const uint16_t* p, int64_t i) {
-  return __uint_as_float((uint32_t)p[i] << 16);
-}
-__device__ __forceinline__ float elem_f32(const float* p, int64_t i) { return p[i]; }
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_t;
 
-// 16 bytes of a K row as floats (8 bf16 or 4 fp32 values)
-__device__ __forceinline__ void row_chunk(const uint16_t* row, int e0, float (&x)[8]) {
-  const uint4 u = load16(row + e0);
-  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    x[2 * i] = __uint_as_float(w[i] << 16);
-    x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ void row_chunk(const float* row, int e0, float (&x)[8]) {
-  const uint4 u = load16(row + e0);
-  x[0] = __uint_as_float(u.x); x[1] = __uint_as_float(u.y);
-  x[2] = __uint_as_float(u.z); x[3] = __uint_as_float(u.w);
-}
-
-template <typename E, int D, bool MASS>
-__global__ __launch_bounds__(kAttThreads) void cache_attention_kernel(AttArgs a) {
-  constexpr int kPer16 = 16 / (int)sizeof(E);                 // elements per 16 bytes
+template <int D, bool MASS>
+__global__ __launch_bounds__(kAttThreads) void cache_attention_f32_kernel(AttArgs a) {
   constexpr int kOwn = (kMaxAttG * D + kAttThreads - 1) / kAttThreads;
   const int row = blockIdx.x;                                 // b * n_q + r
   const int b = row / a.n_q, r = row - b * a.n_q;
@@ -78,17 +61,17 @@ __global__ __launch_bounds__(kAttThreads) void cache_attention_kernel(AttArgs a)
   __shared__ float redm[kMaxAttG][4], reds[kMaxAttG][4];
 
   const int64_t q_rows = (int64_t)a.batch * a.n_q;
-  const E* qb = reinterpret_cast<const E*>(a.q);
+  const float* qb = reinterpret_cast<const float*>(a.q);
   for (int i = tid; i < G * D; i += kAttThreads) {
     const int g = i / D, e = i - g * D;
-    qs[g][e] = elem_f32(qb, ((int64_t)(h * G + g) * q_rows + row) * D + e);
+    qs[g][e] = qb[((int64_t)(h * G + g) * q_rows + row) * D + e];
   }
   const int nk = max(0, min(a.n_kept[b], a.n_select));
   const int nt = max(0, min(a.n_tail, a.n_tail - a.q_from_end + r + 1));
   const int n_vis = nk + nt;                                  // rows [0, n_vis) attended
   const int64_t row0 = ((int64_t)b * a.n_kv_heads + h) * a.n_out;
-  const E* kc = reinterpret_cast<const E*>(a.k) + row0 * D;
-  const E* vc = reinterpret_cast<const E*>(a.v) + row0 * D;
+  const float* kc = reinterpret_cast<const float*>(a.k) + row0 * D;
+  const float* vc = reinterpret_cast<const float*>(a.v) + row0 * D;
 
   // this thread's output elements: e = tid + kAttThreads * i (head e / D, dim e % D;
   // kAttThreads is a multiple of D, so the dim is the same for all of them)
@@ -108,15 +91,15 @@ __global__ __launch_bounds__(kAttThreads) void cache_attention_kernel(AttArgs a)
 #pragma unroll
     for (int g = 0; g < kMaxAttG; ++g) x[g] = 0.0f;
     if (valid) {
-      const E* krow = kc + (int64_t)j * D;
-      for (int e0 = 0; e0 < D; e0 += kPer16) {
-        float kv[8];
-        row_chunk(krow, e0, kv);
+      const float* krow = kc + (int64_t)j * D;
+      for (int e0 = 0; e0 < D; e0 += 4) {
+        const float4 kv4 = *reinterpret_cast<const float4*>(krow + e0);
+        const float kv[4] = {kv4.x, kv4.y, kv4.z, kv4.w};
 #pragma unroll
         for (int g = 0; g < kMaxAttG; ++g)
           if (g < G)
 #pragma unroll
-            for (int t = 0; t < kPer16; ++t) x[g] = fmaf(kv[t], qs[g][e0 + t], x[g]);
+            for (int t = 0; t < 4; ++t) x[g] = fmaf(kv[t], qs[g][e0 + t], x[g]);
       }
     }
     // chunk maxima per head, across the 4 wavefronts
@@ -162,10 +145,10 @@ __global__ __launch_bounds__(kAttThreads) void cache_attention_kernel(AttArgs a)
       const int g = (tid + kAttThreads * i) / D;
       if (g < G) o[i] *= alpha[g];
     }
-    const E* vrow = vc + (int64_t)c0 * D + dim;
+    const float* vrow = vc + (int64_t)c0 * D + dim;
 #pragma unroll 8
     for (int t = 0; t < n_here; ++t) {
-      const float vv = elem_f32(vrow, (int64_t)t * D);
+      const float vv = vrow[(int64_t)t * D];
 #pragma unroll
       for (int i = 0; i < kOwn; ++i) {
         const int g = (tid + kAttThreads * i) / D;
@@ -204,316 +187,401 @@ __global__ __launch_bounds__(kAttThreads) void cache_attention_kernel(AttArgs a)
 }
 
 // ---------------------------------------------------------------------------------------
-// Matrix-core path (bf16; d = 128, or d = 64 for the evicted mass; n_q <= 64).  One
-// workgroup per (query head, sequence): wavefront w takes row tile w % 4 of the head's n_q
-// rows and key pair w / 4 (keys 32 (w / 4) .. +31) of every tile (64 keys and 8 wavefronts
-// for the attention, 128 keys and 16 for the mass), so several wavefronts per SIMD hide
-// each other's latencies; at the end the key pairs of a row tile are merged in LDS in a
-// fixed order.  The G workgroups of a KV head are
+// Matrix-core path (bf16, d = 64 or 128, any number of query rows).  One workgroup per
+// (row block, query head, sequence): a row block is up to three 16-row tiles of the head's
+// n_q rows (the 34 scoring rows are one block), and the workgroup's wavefronts deal the
+// 32-key subtiles of the compacted rows out among themselves, wavefront w taking subtiles
+// w, w + W, w + 2W, ...  Each wavefront keeps its own (reference, sum, output) of every row
+// and nothing is shared until the end, so the loop holds no barrier and every subtile's
+// loads have the wavefront's own softmax and products to land under; the W partial results
+// of a row meet once in LDS, in a fixed order.  The G workgroups of a KV head are
 // consecutive units of the XCD-aware order, so they share one L2 and each compacted row
-// leaves HBM once.  Tiles of the compacted K (and V) are loaded from asm into a ring of
-// register slots (tiles in flight while one is computed; past the end the loads re-read
-// the last row and those tiles are fully masked, so every wait has a fixed count) and
-// stored into double-buffered LDS: K rows XOR-swizzled by row as in the scoring, V
-// transposed to [dim][key] (four keys of one dimension per 8-byte unit, units swizzled by
-// dimension) so that a lane reads the 8 keys of an MFMA operand with two 8-byte loads.
-//   logits:  S^T = K Q^T per 16-key subtile (A = keys, B = query rows): a lane holds 4 keys
-//            of one row; tiles below every row's first invisible key skip the mask;
+// leaves HBM once.
+//   Every load is a global->LDS copy of whole rows (consecutive lanes on consecutive 16-byte
+//   units; loading MFMA fragments straight from global memory puts neighbouring lanes on
+//   different rows, which a compute unit serves at a quarter of the rate: measured 35 bytes
+//   per ns for K alone) into the wavefront's own buffers, kBuf of K and of V:
+//   K: 16-byte units XOR-swizzled by row; a subtile's fragments are read into registers at
+//      once and the buffer is refilled before the products.
+//   V: 32-byte segments XOR-swizzled by row, read as MFMA operands by the transposing LDS
+//      read ds_read_b64_tr_b16, which gives lane c of a 16-lane group four keys of
+//      dimension c; refilled after the products.
+//   Past the wavefront's last subtile the copies read one row of the cache, so every wait has
+//   a fixed count.
+//   logits:  S^T = K Q^T per 16-key half (A = keys, B = query rows): a lane holds 4 keys
+//            of one row; subtiles below every row's first invisible key skip the mask;
 //   softmax: per row a reference m, the same in the row's four lane groups, and a sum per
 //            lane; m moves only when a sum reaches kSumLimit (then to the row's batch
 //            maximum, the sums and outputs rescaled), so the common path is fma, exp2, add;
-//   output:  O^T += V^T P^T per 32 keys (A = V^T from LDS, B = the lane's own 8 weights
-//            from two subtiles), P split into a truncated bf16 high part and the bf16 of
-//            the remainder (two products, ~15 bits of weight); a lane holds 4 dimensions of
-//            its own row, so the rescale of a row is local to the lane.
-// The evicted-mass variant stops after the sums.
-// Tiles of 64 keys and 8 wavefronts (two key pairs) for the attention, whose output
-// accumulators need the registers of two wavefronts per SIMD; 128 keys and 16 wavefronts
-// (four key pairs) for the evicted mass.
-template <int D, bool MASS>
-struct AttMfma {
-  static constexpr int kKT = MASS ? 128 : 64;              // keys per tile
-  static constexpr int kSplit = kKT / 32;                  // key pairs: wavefronts per row tile
-  static constexpr int kThreads = 4 * kSplit * kWave;
+//   output:  O^T += V^T P^T per 32 keys (A = V^T, B = the lane's own 8 weights from the two
+//            halves), P split into a truncated bf16 high part and the bf16 of the remainder
+//            (two products, ~15 bits of weight); a lane holds 4 dimensions of its own row,
+//            so the rescale of a row is local to the lane.
+// The evicted-mass variant (MASS) stops after the sums.
+// What bounds it (MI355X, 34 rows x 32 heads x 8 sequences over 2050 rows each, 256
+// workgroups): every compute unit reads its own 1 MB of K and V, 92 bytes per ns with one row
+// tile (a quarter of that from HBM or the Infinity Cache, the rest its XCD's L2); with three
+// row tiles the products and the softmax of two wavefronts per SIMD (9.2 ns per key, 4.8 of
+// them matrix-core cycles, against 5.6 with one).  Measured, attention 55 -> 28 us, mass with
+// its reduce launch 25 -> 18 us, against the previous kernel (the four row tiles and the key
+// pairs of shared 64-key tiles over the wavefronts, two barriers per tile); 16 rows 18 and 13 us.
+template <int D, int RT, bool MASS>
+struct AttWave {
+  static constexpr int kWaves = 8;
+  static constexpr int kThreads = kWaves * kWave;
+  static constexpr int kPerSimd = kWaves / 4;              // wavefronts per SIMD
+  static constexpr int kBuf = (MASS ? 2 : 1) * (128 / D);  // buffers of K, and of V, per wavefront
+  static constexpr int kSub = 32;                          // keys per subtile
   static constexpr int kRowBytes = D * 2;
-  static constexpr int kUnits = kRowBytes / 16;            // 16-byte units per K row
-  static constexpr int kKBytes = kKT * kRowBytes;          // one K tile
-  static constexpr int kKLoads = kKT * kUnits / kThreads;  // per thread
-  static constexpr int kVBytes = D * kKT * 2;              // one transposed V tile
+  static constexpr int kUnits = kRowBytes / 16;            // 16-byte units per row
   static constexpr int kNS = D / 32;                       // MFMA steps over d
   static constexpr int kDT = D / 16;                       // 16-dimension output tiles
+  static constexpr int kSubBytes = kSub * kRowBytes;       // one subtile of K or of V
+  static constexpr int kCopies = kSubBytes / (kWave * 16); // copy instructions per subtile
+  static constexpr int kVCopies = MASS ? 0 : kCopies;
+  static constexpr int kWaveBytes = (MASS ? 1 : 2) * kBuf * kSubBytes;
+  static constexpr int kQBytes = RT * 16 * kRowBytes;      // the block's query rows
+  static constexpr int kMergeTiles = MASS ? 1 : (RT < 2 ? RT : 2);   // row tiles merged at once
+  static constexpr int kMergeBytes = MASS ? 0 : kMergeTiles * kWaves * 16 * D * 4;
+  static constexpr int kRingBytes = kWaves * kWaveBytes;
+  static constexpr int kArea = kRingBytes > kMergeBytes ? kRingBytes : kMergeBytes;
+  static constexpr int kLdsBytes = kArea + kQBytes;
 };
 
-template <int D, bool MASS>
-__global__ __launch_bounds__((AttMfma<D, MASS>::kThreads)) void cache_attention_mfma_kernel(AttArgs a) {
-  using AT = AttMfma<D, MASS>;
-  constexpr int kAttKT = AT::kKT, kAttSplit = AT::kSplit, kAttMfmaThreads = AT::kThreads;
-  constexpr int NS = AT::kNS;
-  static_assert(MASS || (D == 128 && kAttKT * 16 == 2 * kAttMfmaThreads),
-                "the V transpose: 128 dimensions (16 x 8), a key pair per thread");
-  static_assert(AT::kKLoads >= 1 && AT::kKLoads * kAttMfmaThreads == kAttKT * AT::kUnits, "K staging");
-  const int units = a.batch * a.n_kv_heads * a.G;
+// Row of the swizzle of V row r: its 32-byte segment s is kept at segment s ^ att_swz(r), so
+// that the 8 rows of half a transposing read fall on all 64 banks.
+template <int D>
+__device__ __forceinline__ int att_swz(int r) {
+  return D == 128 ? (r & 7) : ((r >> 1) & 3);
+}
+
+template <int D, int RT, bool MASS>
+__global__ __launch_bounds__((AttWave<D, RT, MASS>::kThreads), (AttWave<D, RT, MASS>::kPerSimd))
+void cache_attention_wave_kernel(AttArgs a) {
+  using AT = AttWave<D, RT, MASS>;
+  constexpr int NS = AT::kNS, W = AT::kWaves;
+  const int units = a.batch * a.n_kv_heads * a.G * a.row_blocks;
   const int unit = xcd_unit(units);
   if (unit >= units) return;
-  const int hq = unit % (a.n_kv_heads * a.G), b = unit / (a.n_kv_heads * a.G);
+  const int rb = unit % a.row_blocks, hb = unit / a.row_blocks;
+  const int hq = hb % (a.n_kv_heads * a.G), b = hb / (a.n_kv_heads * a.G);
   const int h = hq / a.G;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wvu = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rt = wvu & 3, ks = wvu >> 2;                       // row tile, key pair
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g16 = lane >> 4, c16 = lane & 15;
-  const bool own = rt * 16 < a.n_q;                            // wave-uniform
+  const int r0 = rb * RT * 16;                                 // first row of the block
   const int64_t q_rows = (int64_t)a.batch * a.n_q;
+  const int64_t row_base = (int64_t)hq * q_rows + (int64_t)b * a.n_q;
   const int nk = max(0, min(a.n_kept[b], a.n_select));
-  const int n_vis_max = nk + max(0, min(a.n_tail, a.n_tail - a.q_from_end + a.n_q));
-  const int n_vis_min = nk + max(0, min(a.n_tail, a.n_tail - a.q_from_end + 1));
+  const int r_last = min(a.n_q, r0 + RT * 16) - 1;             // last row of the block
+  auto visible = [&](int r) { return nk + max(0, min(a.n_tail, a.n_tail - a.q_from_end + r + 1)); };
+  const int n_vis_max = visible(r_last), n_vis_min = visible(r0);
   const int64_t row0 = ((int64_t)b * a.n_kv_heads + h) * a.n_out;
   const char* kc = reinterpret_cast<const char*>(a.k) + row0 * AT::kRowBytes;
   const char* vc = MASS ? nullptr : reinterpret_cast<const char*>(a.v) + row0 * AT::kRowBytes;
-  constexpr int kStageBytes = AT::kKBytes + (MASS ? 0 : AT::kVBytes);
-  __shared__ __attribute__((aligned(16))) char lds[2 * kStageBytes];
-  __shared__ float mfin[kAttSplit][4][16], sfin[kAttSplit][4][16];
+  __shared__ __attribute__((aligned(1024))) char lds[AT::kLdsBytes];
+  __shared__ float mfin[W][RT * 16], sfin[W][RT * 16], mrow[RT * 16], irow[RT * 16];
 
-  const int r = rt * 16 + c16;                                 // this lane's row
   if (n_vis_max == 0) {                                        // nothing visible: no loads
-    if (ks == 0 && own && r < a.n_q) {
-      const int64_t ri = (int64_t)hq * q_rows + (int64_t)b * a.n_q + r;
+    for (int r = r0 + wv; r <= r_last; r += W) {
       if constexpr (MASS) {
-        if (g16 == 0) a.rho[ri] = 1.0f;
+        if (lane == 0) a.rho[row_base + r] = 1.0f;
       } else {
-        if (g16 == 0) a.lse[ri] = -INFINITY;
-        for (int e = 4 * g16; e < D; e += 16)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) a.out[ri * D + e + q] = 0.0f;
+        if (lane == 0) a.lse[row_base + r] = -INFINITY;
+        for (int e = lane; e < D; e += kWave) a.out[(row_base + r) * D + e] = 0.0f;
       }
     }
     return;
   }
-  const uint16_t* qrow = reinterpret_cast<const uint16_t*>(a.q) +
-                         ((int64_t)hq * q_rows + (int64_t)b * a.n_q + min(r, a.n_q - 1)) * D;
-  u32x4_t qf[NS];
-#pragma unroll
-  for (int st = 0; st < NS; ++st) qf[st] = async_load16(reinterpret_cast<const char*>(qrow) + (st * 4 + g16) * 16);
-  const int lim = r < a.n_q ? nk + max(0, min(a.n_tail, a.n_tail - a.q_from_end + r + 1)) : 0;
-  float m = kLazyRefInit, ssum = 0.0f;
-  f32x4_t o[MASS ? 1 : AT::kDT];
-#pragma unroll
-  for (int dt = 0; dt < (MASS ? 1 : AT::kDT); ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // tile staging: K units (kKLoads per thread) and, for the attention, keys 2 (tid / 16),
-  // +1 of V at dimensions 8 (tid % 16) .. +7, stored as the 4-byte halves of V^T units
-  constexpr int PF = MASS ? 4 : 3;                             // tiles in flight
-  constexpr int NV = MASS ? 0 : 2;
-  constexpr int LPT = AT::kKLoads + NV;                        // loads per tile per thread
-  u32x4_t kst[PF][AT::kKLoads], vst[PF][MASS ? 1 : NV];
-  const int vp = tid >> 4, vo = tid & 15;
-  auto stage_load = [&](int t, u32x4_t (&kr)[AT::kKLoads], u32x4_t (&vr)[MASS ? 1 : NV]) {
-    const int j0 = t * kAttKT;
+  float m[RT], ssum[RT];
+  f32x4_t o[MASS ? 1 : RT][MASS ? 1 : AT::kDT];
 #pragma unroll
-    for (int i = 0; i < AT::kKLoads; ++i) {
-      const int e = tid + kAttMfmaThreads * i;
-      const int rr = e / AT::kUnits, u = e % AT::kUnits;
-      kr[i] = async_load16(kc + (int64_t)max(0, min(j0 + rr, n_vis_max - 1)) * AT::kRowBytes + u * 16);
+  for (int i = 0; i < RT; ++i) {
+    m[i] = kLazyRefInit;
+    ssum[i] = 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < (MASS ? 1 : RT); ++i)
+#pragma unroll
+    for (int dt = 0; dt < (MASS ? 1 : AT::kDT); ++dt) o[i][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  // the full-cache log-partition of row tid, before the copies: it is needed at the very end
+  // and would otherwise cost a round trip of its own there
+  float full = 0.0f;
+  if constexpr (MASS) full = async_load4(a.lse_full + row_base + min(r0 + tid, r_last));
+
+  // the block's query rows (rows past its last one read that row; their results are dropped)
+  char* qlds = lds + AT::kArea;
+  {
+    const char* qb = reinterpret_cast<const char*>(a.q) + (row_base + r0) * AT::kRowBytes;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)qlds);
+    for (int i = wv; i < AT::kQBytes / (kWave * 16); i += W) {
+      const int e = i * kWave + lane, r = e / AT::kUnits, u = (e % AT::kUnits) ^ (r % AT::kUnits);
+      dma16_sbase(qb, (uint32_t)(min(r, r_last - r0) * AT::kRowBytes + u * 16), dst + i * kWave * 16);
     }
-    if constexpr (!MASS) {
+  }
+
+  const int nt = (n_vis_max + AT::kSub - 1) / AT::kSub;
+  char* kbuf = lds + wv * AT::kWaveBytes;                      // [kBuf] K subtiles, then V's
+  char* vbuf = kbuf + AT::kBuf * AT::kSubBytes;
+  // Copy of subtile t's rows of base: lane l of instruction i fills 16-byte position
+  // e = 64 i + l and fetches the unit that belongs there.  The unit's offset within the
+  // instruction's kilobyte repeats every P instructions and is kept (off); a subtile that
+  // reaches past the last visible row derives clamped rows instead (rows past it read it,
+  // those keys are masked; a subtile past the end reads row 0), from a lane number that the
+  // empty asm keeps out of the loop's registers.
+  constexpr int PK = D == 128 ? 4 : 1, PV = D == 128 ? 2 : 1;
+  auto swz_k = [](int r, int p) { return p ^ (r % AT::kUnits); };
+  auto swz_v = [](int r, int p) { return (((p >> 1) ^ att_swz<D>(r)) << 1) | (p & 1); };
+  uint32_t off_k[PK], off_v[MASS ? 1 : PV];
 #pragma unroll
-      for (int k = 0; k < 2; ++k)
-        vr[k] = async_load16(vc + (int64_t)max(0, min(j0 + 2 * vp + k, n_vis_max - 1)) * AT::kRowBytes + vo * 16);
-    }
-  };
-  auto stage_store = [&](int buf, u32x4_t (&kr)[AT::kKLoads], u32x4_t (&vr)[MASS ? 1 : NV]) {
-    char* kl = lds + buf * kStageBytes;
+  for (int i = 0; i < PK; ++i) {
+    const int e = i * kWave + lane, r = e / AT::kUnits;
+    off_k[i] = (uint32_t)((r * AT::kUnits + swz_k(r, e % AT::kUnits)) * 16 - i * kWave * 16);
+  }
 #pragma unroll
-    for (int i = 0; i < AT::kKLoads; ++i) {
-      reg_fence(kr[i]);
-      const int e = tid + kAttMfmaThreads * i;
-      const int rr = e / AT::kUnits, u = e % AT::kUnits;
-      *reinterpret_cast<uint4*>(kl + rr * AT::kRowBytes + ((u ^ (rr % AT::kUnits)) * 16)) = as_uint4(kr[i]);
-    }
-    if constexpr (!MASS) {
-      char* vl = kl + AT::kKBytes;
-      reg_fence(vr[0]);
-      reg_fence(vr[1]);
-      const int quad = vp >> 1, hpos = (vp & 1) * 4;
+  for (int i = 0; i < (MASS ? 1 : PV); ++i) {
+    const int e = i * kWave + lane, r = e / AT::kUnits;
+    off_v[i] = (uint32_t)((r * AT::kUnits + swz_v(r, e % AT::kUnits)) * 16 - i * kWave * 16);
+  }
+  auto copy = [&](const char* base, int t, char* buf, const uint32_t* off, int P, auto swz) {
+    const bool real = t < nt;                                  // wave-uniform
+    base += real ? (int64_t)t * AT::kSubBytes : 0;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)buf);
+    if (t * AT::kSub + AT::kSub <= n_vis_max) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < AT::kCopies; ++i)
+        dma16_sbase(base + i * kWave * 16, off[i % P], dst + i * kWave * 16);
+    } else {
+      const int last = real ? n_vis_max - 1 - t * AT::kSub : 0;
+      int l = lane;
+      asm volatile("" : "+v"(l));
 #pragma unroll
-        for (int odd = 0; odd < 2; ++odd) {
-          const int d = 8 * vo + 2 * i + odd;
-          *reinterpret_cast<uint32_t*>(vl + d * (kAttKT * 2) + ((quad ^ (d & 15)) * 8) + hpos) =
-              __builtin_amdgcn_perm(vr[1][i], vr[0][i], odd ? 0x07060302u : 0x05040100u);
-        }
+      for (int i = 0; i < AT::kCopies; ++i) {
+        const int e = i * kWave + l, r = e / AT::kUnits;
+        dma16_sbase(base, (uint32_t)((min(r, last) * AT::kUnits + swz(r, e % AT::kUnits)) * 16),
+                    dst + i * kWave * 16);
       }
     }
   };
+  auto copy_k = [&](int t, int s) { copy(kc, t, kbuf + s * AT::kSubBytes, off_k, PK, swz_k); };
+  auto copy_v = [&](int t, int s) {
+    if constexpr (!MASS) copy(vc, t, vbuf + s * AT::kSubBytes, off_v, PV, swz_v);
+  };
 
-  auto compute = [&](int t, int buf) {
-    if (!own) return;
-    const char* kl = lds + buf * kStageBytes;
-    const int j0 = t * kAttKT + 32 * ks;                       // this wavefront's 32 keys
-    const bool masked = j0 + 32 > n_vis_min;                    // uniform: some key may be hidden
-    float x[8];
+  // kBuf subtiles of K and V in flight, K before V
+  constexpr int kAhead = AT::kBuf * (AT::kCopies + AT::kVCopies);
 #pragma unroll
-    for (int su = 0; su < 2; ++su) {
-      const int kr = 32 * ks + 16 * su + c16;
-      uint4 kf[NS];
+  for (int s = 0; s < AT::kBuf; ++s) {
+    copy_k(wv + s * W, s);
+    copy_v(wv + s * W, s);
+  }
+  asm_wait_vmcnt<kAhead>();                                    // the query rows and full
+  if constexpr (MASS) reg_fence(full);
+  wg_barrier();
+  u32x4_t qf[RT][NS];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+      const int r = i * 16 + c16;
+      qf[i][st] = __builtin_bit_cast(
+          u32x4_t, load16(qlds + r * AT::kRowBytes + (((st * 4 + g16) ^ (r % AT::kUnits)) * 16)));
+    }
+
+  for (int t0 = wv; t0 < nt; t0 += AT::kBuf * W) {
+#pragma unroll
+   for (int s = 0; s < AT::kBuf; ++s) {
+    const int t = t0 + s * W;
+    asm_wait_vmcnt<kAhead - AT::kCopies>();                    // K of subtile t
+    uint4 kf[2][NS];
+#pragma unroll
+    for (int su = 0; su < 2; ++su)
+#pragma unroll
+      for (int st = 0; st < NS; ++st) {
+        const int r = 16 * su + c16;
+        kf[su][st] = load16(kbuf + s * AT::kSubBytes + r * AT::kRowBytes +
+                            (((st * 4 + g16) ^ (r % AT::kUnits)) * 16));
+      }
+    wait_lgkmcnt0();                                           // fragments in registers
+    copy_k(t + AT::kBuf * W, s);
+    const int j0 = t * AT::kSub;
+    uint4 ph[MASS ? 1 : RT], pl[MASS ? 1 : RT];
+    if (t < nt) {                                              // wave-uniform
+    const bool masked = j0 + AT::kSub > n_vis_min;             // some key may be hidden
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
       for (int st = 0; st < NS; ++st)
-        kf[st] = *reinterpret_cast<const uint4*>(kl + kr * AT::kRowBytes + (((st * 4 + g16) ^ (kr % AT::kUnits)) * 16));
-      f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int st = 0; st < NS; ++st) acc = mma_step(bf16_t{}, kf[st], as_uint4(qf[st]), acc);
-      // acc[q] = logit of key j0 + 16 su + 4 g16 + q for this lane's row
+        for (int su = 0; su < 2; ++su) acc[su] = mma_step(bf16_t{}, kf[su][st], as_uint4(qf[i][st]), acc[su]);
+      // x[4 su + q] = logit of key j0 + 16 su + 4 g16 + q for this lane's row of tile i
+      float x[8];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int j = j0 + 16 * su + 4 * g16 + q;
-        x[4 * su + q] = (!masked || j < lim) ? acc[q] : -INFINITY;
-      }
-    }
-    float pv[8], ps = 0.0f;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      pv[q] = fast_exp2(fmaf(x[q], a.scale_log2, -m));
-      ps += pv[q];
-    }
-    float ns = ssum + ps;
-    // a row whose sum (in any of its lane groups) reaches kSumLimit moves its reference,
-    // the same in all four lane groups
-    int ov = !(ns < kSumLimit) ? 1 : 0;
-    if (__any(ov)) {
-      ov |= __shfl_xor(ov, 16, 64);
-      ov |= __shfl_xor(ov, 32, 64);
-      float mx = x[0];
-#pragma unroll
-      for (int q = 1; q < 8; ++q) mx = fmaxf(mx, x[q]);
-      mx *= a.scale_log2;
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (ov) {
-        const float nr = fmaxf(mx, m + kLazyBound);
-        const float f = fast_exp2(m - nr);
-        ps = 0.0f;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          pv[q] = fast_exp2(fmaf(x[q], a.scale_log2, -nr));
-          ps += pv[q];
-        }
-        ns = ssum * f + ps;
-        if constexpr (!MASS) {
-#pragma unroll
-          for (int dt = 0; dt < AT::kDT; ++dt)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) o[dt][q] *= f;
-        }
-        m = nr;
-      }
-    }
-    ssum = ns;
-    if constexpr (!MASS) {
-      // P ~ hi + lo: hi = the upper half of each float (a bf16 truncation), lo = the
-      // remainder, also truncated; packed two weights per register
-      uint32_t hb[4], lb[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t u0 = __float_as_uint(pv[2 * q]), u1 = __float_as_uint(pv[2 * q + 1]);
-        const float l0 = pv[2 * q] - __uint_as_float(u0 & 0xffff0000u);
-        const float l1 = pv[2 * q + 1] - __uint_as_float(u1 & 0xffff0000u);
-        hb[q] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
-        lb[q] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
-      }
-      const uint4 ph = make_uint4(hb[0], hb[1], hb[2], hb[3]);
-      const uint4 pl = make_uint4(lb[0], lb[1], lb[2], lb[3]);
-      const char* vl = kl + AT::kKBytes;
-#pragma unroll
-      for (int dt = 0; dt < AT::kDT; ++dt) {
-        const int d = dt * 16 + c16;
-        const char* vrow = vl + d * (kAttKT * 2);
-        const uint2 v0 = *reinterpret_cast<const uint2*>(vrow + (((8 * ks + g16) ^ (d & 15)) * 8));
-        const uint2 v1 = *reinterpret_cast<const uint2*>(vrow + (((8 * ks + 4 + g16) ^ (d & 15)) * 8));
-        const uint4 vf = make_uint4(v0.x, v0.y, v1.x, v1.y);
-        o[dt] = mma_step(bf16_t{}, vf, ph, o[dt]);
-        o[dt] = mma_step(bf16_t{}, vf, pl, o[dt]);
-      }
-    }
-  };
-
-  // Whole rounds of PF tiles: the loads of tile t + PF are issued while tile t is computed,
-  // so the PF - 1 younger tiles' loads are always in flight when tile t's are awaited and
-  // every wait has a fixed count; the first wait also covers the query fragments.
-  const int nt = (n_vis_max + kAttKT - 1) / kAttKT;
-  const int rounds = (nt + PF - 1) / PF;
-#pragma unroll
-  for (int p = 0; p < PF; ++p) stage_load(p, kst[p], vst[p]);
-  asm_wait_vmcnt<(PF - 1) * LPT>();
-#pragma unroll
-  for (int st = 0; st < NS; ++st) reg_fence(qf[st]);
-  for (int rd = 0; rd < rounds; ++rd) {
-#pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      const int t = rd * PF + p;
-      if (p > 0) asm_wait_vmcnt<(PF - 1) * LPT>();        // tile t's loads have landed
-      stage_store(t & 1, kst[p], vst[p]);
-      __syncthreads();
-      stage_load(t + PF, kst[p], vst[p]);
-      compute(t, t & 1);
-      __syncthreads();
-    }
-    asm_wait_vmcnt<(PF - 1) * LPT>();                    // the next round's first tile
-  }
-  asm_wait_vmcnt<0>();                                   // no load still writes a register
-
-  // merge the four key pairs of each row: references and sums first, then the outputs
-  // (through the staging buffers, which are free after the loop's last barrier)
-  float st = ssum;
-  st += __shfl_xor(st, 16, 64);
-  st += __shfl_xor(st, 32, 64);
-  if (own && g16 == 0) {
-    mfin[ks][rt][c16] = m;
-    sfin[ks][rt][c16] = st;
-  }
-  float* ofin = reinterpret_cast<float*>(lds);                 // [ks][rt][16 rows][D]
-  static_assert(MASS || kAttSplit * 4 * 16 * D * 4 <= 2 * kStageBytes, "output merge area");
-  if constexpr (!MASS) {
-    if (own) {
-#pragma unroll
-      for (int dt = 0; dt < AT::kDT; ++dt)
+      for (int su = 0; su < 2; ++su)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          ofin[((ks * 4 + rt) * 16 + c16) * D + dt * 16 + 4 * g16 + q] = o[dt][q];
+          x[4 * su + q] = acc[su][q];
+      if (masked) {
+        // the row's limit is derived here (the empty asm keeps it out of the loop's registers)
+        int r = r0 + i * 16 + c16;
+        asm volatile("" : "+v"(r));
+        const int lim = visible(min(r, r_last));
+#pragma unroll
+        for (int su = 0; su < 2; ++su)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (j0 + 16 * su + 4 * g16 + q >= lim) x[4 * su + q] = -INFINITY;
+      }
+      float pv[8];
+      auto weigh = [&](float ref) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) pv[q] = fast_exp2(fmaf(x[q], a.scale_log2, -ref));
+        return ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
+      };
+      float ns = ssum[i] + weigh(m[i]);
+      // a row whose sum (in any of its lane groups) reaches kSumLimit moves its reference,
+      // the same in all four lane groups
+      int ov = !(ns < kSumLimit) ? 1 : 0;
+      if (__any(ov)) {
+        ov |= __shfl_xor(ov, 16, 64);
+        ov |= __shfl_xor(ov, 32, 64);
+        float mx = x[0];
+#pragma unroll
+        for (int q = 1; q < 8; ++q) mx = fmaxf(mx, x[q]);
+        mx *= a.scale_log2;
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        if (ov) {
+          const float nr = fmaxf(mx, m[i] + kLazyBound);
+          const float f = fast_exp2(m[i] - nr);
+          ns = ssum[i] * f + weigh(nr);
+          if constexpr (!MASS) {
+#pragma unroll
+            for (int dt = 0; dt < AT::kDT; ++dt)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) o[i][dt][q] *= f;
+          }
+          m[i] = nr;
+        }
+      }
+      ssum[i] = ns;
+      if constexpr (!MASS) {
+        // P ~ hi + lo: hi = the upper half of each float (a bf16 truncation), lo = the
+        // remainder, also truncated; packed two weights per register
+        uint32_t hb[4], lb[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t u0 = __float_as_uint(pv[2 * q]), u1 = __float_as_uint(pv[2 * q + 1]);
+          const float l0 = pv[2 * q] - __uint_as_float(u0 & 0xffff0000u);
+          const float l1 = pv[2 * q + 1] - __uint_as_float(u1 & 0xffff0000u);
+          hb[q] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+          lb[q] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+        }
+        ph[i] = make_uint4(hb[0], hb[1], hb[2], hb[3]);
+        pl[i] = make_uint4(lb[0], lb[1], lb[2], lb[3]);
+      }
+    }
+    }
+    if constexpr (!MASS) {
+      asm_wait_vmcnt<kAhead - AT::kVCopies>();                 // V of subtile t
+      // V^T operand of dimension tile dt: lane group g16's keys 4 g16 .. +3 of each half; all
+      // of them go to registers (K's are free by now) so that the buffer refills at once
+      const int vr = 4 * g16 + (c16 >> 2);
+      const uint32_t va = (uint32_t)(uintptr_t)(lds_ptr_t)(vbuf + s * AT::kSubBytes) +
+                          vr * AT::kRowBytes + att_swz<D>(vr) * 32 + (c16 & 3) * 8;
+      uint4 vf[AT::kDT];
+#pragma unroll
+      for (int dt = 0; dt < AT::kDT; ++dt) {
+        const uint32_t at = va ^ (dt * 32);
+        const uint2 w0 = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4_t)(uintptr_t)at));
+        const uint2 w1 = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4_t)(uintptr_t)(at + 16 * AT::kRowBytes)));
+        vf[dt] = make_uint4(w0.x, w0.y, w1.x, w1.y);
+      }
+      wait_lgkmcnt0();
+      copy_v(t + AT::kBuf * W, s);
+      if (t < nt) {
+#pragma unroll
+        for (int dt = 0; dt < AT::kDT; ++dt)
+#pragma unroll
+          for (int i = 0; i < RT; ++i) {
+            o[i][dt] = mma_step(bf16_t{}, vf[dt], ph[i], o[i][dt]);
+            o[i][dt] = mma_step(bf16_t{}, vf[dt], pl[i], o[i][dt]);
+          }
+      }
+    }
+   }
+  }
+  asm_wait_vmcnt<0>();                                         // no copy still writes
+
+  // the wavefronts' references and sums of each row, then their outputs, two row tiles at
+  // a time through the ring area (16-byte units XOR-swizzled by row)
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    float st = ssum[i];
+    st += __shfl_xor(st, 16, 64);
+    st += __shfl_xor(st, 32, 64);
+    if (g16 == 0) {
+      mfin[wv][i * 16 + c16] = m[i];
+      sfin[wv][i * 16 + c16] = st;
     }
   }
   __syncthreads();
-  if (ks != 0 || !own || r >= a.n_q) return;
-  float mf = mfin[0][rt][c16];
+  if (tid < RT * 16) {                                         // row tid of the block
+    float mf = mfin[0][tid], sf = 0.0f;
 #pragma unroll
-  for (int k = 1; k < kAttSplit; ++k) mf = fmaxf(mf, mfin[k][rt][c16]);
-  float w[kAttSplit], sf = 0.0f;
+    for (int w = 1; w < W; ++w) mf = fmaxf(mf, mfin[w][tid]);
 #pragma unroll
-  for (int k = 0; k < kAttSplit; ++k) {
-    w[k] = rescale(mfin[k][rt][c16], mf);
-    sf += sfin[k][rt][c16] * w[k];
-  }
-  const bool seen = sf > 0.0f;
-  const float lse_r = seen ? (mf + __log2f(sf)) * 0.6931471805599453f : -INFINITY;
-  const int64_t ri = (int64_t)hq * q_rows + (int64_t)b * a.n_q + r;
-  if constexpr (MASS) {
-    if (g16 == 0) {
+    for (int w = 0; w < W; ++w) sf += sfin[w][tid] * rescale(mfin[w][tid], mf);
+    const float lse_r = sf > 0.0f ? (mf + __log2f(sf)) * 0.6931471805599453f : -INFINITY;
+    if (r0 + tid <= r_last) {
       // deficit log Z - log Z_R >= 0 (rounding can leave it a hair below 0)
-      const float dlt = fmaxf(a.lse_full[ri] - lse_r, 0.0f);
-      a.rho[ri] = -expm1f(-dlt);
+      if constexpr (MASS) a.rho[row_base + r0 + tid] = -expm1f(-fmaxf(full - lse_r, 0.0f));
+      else a.lse[row_base + r0 + tid] = lse_r;
     }
-  } else {
-    if (g16 == 0) a.lse[ri] = lse_r;
-    const float inv = seen ? 1.0f / sf : 0.0f;
+    if constexpr (!MASS) {
+      mrow[tid] = mf;
+      irow[tid] = sf > 0.0f ? 1.0f / sf : 0.0f;
+    }
+  }
+  if constexpr (!MASS) {
+    constexpr int U = D / 4;                                   // 16-byte units per output row
+    constexpr int MT = AT::kMergeTiles;
+    float4* area = reinterpret_cast<float4*>(lds);             // [tile][wavefront][16 rows][U]
+    __syncthreads();
 #pragma unroll
-    for (int dt = 0; dt < AT::kDT; ++dt)
+    for (int i0 = 0; i0 < RT; i0 += MT) {
+      if (i0 > 0) __syncthreads();                             // the previous tiles are read
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = dt * 16 + 4 * g16 + q;
-        float acc = 0.0f;
+      for (int i = i0; i < i0 + MT && i < RT; ++i) {
+        const float f = rescale(m[i], mrow[i * 16 + c16]);
 #pragma unroll
-        for (int k = 0; k < kAttSplit; ++k) acc += ofin[((k * 4 + rt) * 16 + c16) * D + e] * w[k];
-        a.out[ri * D + e] = acc * inv;
+        for (int dt = 0; dt < AT::kDT; ++dt)
+          area[(((i - i0) * W + wv) * 16 + c16) * U + ((dt * 4 + g16) ^ c16)] =
+              make_float4(o[i][dt][0] * f, o[i][dt][1] * f, o[i][dt][2] * f, o[i][dt][3] * f);
       }
+      __syncthreads();
+      const int rows = min(MT * 16, r_last + 1 - r0 - i0 * 16);   // rows of these tiles to write
+      for (int e = tid; e < rows * U; e += AT::kThreads) {
+        const int row = e / U, u = e % U, c = row & 15;
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          const float4 p = area[(((row >> 4) * W + w) * 16 + c) * U + (u ^ c)];
+          sum.x += p.x;
+          sum.y += p.y;
+          sum.z += p.z;
+          sum.w += p.w;
+        }
+        const float inv = irow[i0 * 16 + row];
+        *reinterpret_cast<float4*>(a.out + (row_base + r0 + i0 * 16 + row) * D + 4 * u) =
+            make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv);
+      }
+    }
   }
 }
 
@@ -541,39 +609,42 @@ __global__ __launch_bounds__(64) void mass_reduce_kernel(AttArgs a) {
   }
 }
 
-template <typename E, int D, bool MASS>
-hipError_t launch_att(const AttArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((cache_attention_kernel<E, D, MASS>), dim3(a.batch * a.n_q, a.n_kv_heads),
+template <int D, bool MASS>
+hipError_t launch_att_f32(const AttArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL((cache_attention_f32_kernel<D, MASS>), dim3(a.batch * a.n_q, a.n_kv_heads),
                      dim3(kAttThreads), 0, st, a);
   if constexpr (MASS)
     hipLaunchKernelGGL(mass_reduce_kernel, dim3(a.batch, a.n_kv_heads), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
-template <int D, bool MASS>
-hipError_t launch_att_mfma(const AttArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((cache_attention_mfma_kernel<D, MASS>),
-                     dim3(xcd_grid(a.batch * a.n_kv_heads * a.G)), dim3(AttMfma<D, MASS>::kThreads), 0,
-                     st, a);
+template <int D, int RT, bool MASS>
+hipError_t launch_att_wave(const AttArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL((cache_attention_wave_kernel<D, RT, MASS>),
+                     dim3(xcd_grid(a.batch * a.n_kv_heads * a.G * a.row_blocks)),
+                     dim3((AttWave<D, RT, MASS>::kThreads)), 0, st, a);
   if constexpr (MASS)
     hipLaunchKernelGGL(mass_reduce_kernel, dim3(a.batch, a.n_kv_heads), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
+// Row blocks of at most three 16-row tiles (what a wavefront's registers hold next to the
+// outputs), as equal as they come: 4 tiles are two blocks of two.
+template <int D, bool MASS>
+hipError_t launch_att_blocks(AttArgs a, hipStream_t st) {
+  const int tiles = (a.n_q + 15) / 16;
+  a.row_blocks = (tiles + 2) / 3;
+  const int rt = (tiles + a.row_blocks - 1) / a.row_blocks;
+  if (rt == 1) return launch_att_wave<D, 1, MASS>(a, st);
+  if (rt == 2) return launch_att_wave<D, 2, MASS>(a, st);
+  return launch_att_wave<D, 3, MASS>(a, st);
+}
+
 template <bool MASS>
 hipError_t launch_att_typed(const dge_geom_t& g, const AttArgs& a, hipStream_t st) {
-  // the matrix-core path: bf16, at most 64 query rows (a row tile per wavefront), d = 128
-  // (or 64 for the evicted mass)
-  if (g.dtype == DGE_BF16 && a.n_q >= 1 && a.n_q <= 64) {
-    if (g.head_dim == 128) return launch_att_mfma<128, MASS>(a, st);
-    if constexpr (MASS) {
-      if (g.head_dim == 64) return launch_att_mfma<64, true>(a, st);
-    }
-  }
   if (g.dtype == DGE_BF16)
-    return g.head_dim == 128 ? launch_att<uint16_t, 128, MASS>(a, st)
-                             : launch_att<uint16_t, 64, MASS>(a, st);
-  return g.head_dim == 128 ? launch_att<float, 128, MASS>(a, st) : launch_att<float, 64, MASS>(a, st);
+    return g.head_dim == 128 ? launch_att_blocks<128, MASS>(a, st) : launch_att_blocks<64, MASS>(a, st);
+  return g.head_dim == 128 ? launch_att_f32<128, MASS>(a, st) : launch_att_f32<64, MASS>(a, st);
 }
 
 }  // namespace

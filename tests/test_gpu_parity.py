@@ -745,6 +745,53 @@ def test_cache_attention_eq1_and_evicted_mass():
     assert err < 2e-4
 
 
+# (head dim, H_q, H_kv, query rows, tail, kept rows per sequence): row blocks of one to three
+# 16-row tiles and several blocks; caches shorter than a 32-key subtile, exactly one round of
+# the 8 wavefronts, one key more, and a sequence that keeps nothing.
+ATT_WAVE_CASES = [
+    (128, 4, 1, 1, 3, (0, 28, 29, 61)),
+    (128, 8, 2, 16, 16, (240, 241, 0)),
+    (128, 4, 2, 17, 34, (222, 500)),
+    (128, 8, 1, 33, 40, (7, 600)),
+    (128, 2, 1, 49, 64, (100, 448)),
+    (128, 2, 2, 70, 70, (33, 700)),
+    (64, 8, 2, 1, 2, (30, 255)),
+    (64, 4, 2, 34, 34, (0, 222, 734)),
+    (64, 2, 1, 113, 113, (15, 300)),
+]
+
+
+@pytest.mark.parametrize("d,hq,hkv,n_q,tail,kept", ATT_WAVE_CASES)
+def test_cache_attention_row_blocks_vs_oracle(d, hq, hkv, n_q, tail, kept):
+    """Attention and evicted mass of bf16 caches at the edges of the kernel's row blocks and
+    key subtiles, the causal rows and the decode rows, against the oracle."""
+    _log(f"cache attention d={d} heads={hq}/{hkv} n_q={n_q} tail={tail} kept={kept}")
+    rng = np.random.default_rng(500 + n_q + d)
+    B, n_sel = len(kept), max(max(kept), 1)
+    g = dge.Geometry(hq, hkv, d, tail, 0, [n_sel + tail] * B, device=DEV)
+    bits = lambda *s: di.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))  # noqa: E731
+    qb, kb, vb = bits(hq, B * n_q, d), bits(B, hkv, n_sel + tail, d), bits(B, hkv, n_sel + tail, d)
+    q64, k64, v64 = (di.bf16_bits_to_f32(b).astype(np.float64) for b in (qb, kb, vb))
+    q, kc, vc = (to_dev(b, "bf16") for b in (qb, kb, vb))
+    nk = torch.tensor(list(kept) + [0] * 4, dtype=torch.int32, device=DEV)[:max(B, 4)]
+    for from_end in (n_q, 0):
+        out, lse = dge.cache_attention(g, q, n_q, from_end, kc, vc, n_sel, tail, nk)
+        torch.cuda.synchronize()
+        wo, wl = oracle.cache_attention(q64, k64, v64, kept, tail, from_end, hq, hkv)
+        _check_att(out, lse, wo, wl, f"from_end={from_end}")
+        if from_end == n_q:
+            lost = np.asarray(rng.random(wl.shape) * 0.9, np.float64)
+            full = torch.from_numpy((wl - np.log1p(-lost)).astype(np.float32)).to(DEV)
+            rho, beta, l_match = dge.evicted_mass(g, q, n_q, n_q, kc, n_sel, tail, nk, full)
+            torch.cuda.synchronize()
+            # two float32 log-partitions of size <= 16 differ by at most a few 2^-20
+            assert np.abs(rho.cpu().numpy() - lost).max() <= 2e-5
+            per = lost.reshape(hkv, hq // hkv, B, n_q)
+            assert np.abs(beta.cpu().numpy() - per.mean((1, 3)).T).max() <= 2e-5
+            want = (-np.log1p(-per)).mean((1, 3)).T
+            assert np.abs(l_match.cpu().numpy() - want).max() <= 2e-4
+
+
 MASS_CASES = {
     "c2_two_seqs": (di.small_variant("c2", [900, 1400]), None),
     "c1_f32_d64": (di.WORKLOADS["c1"], None),
