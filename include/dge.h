@@ -96,7 +96,10 @@ int dge_abi_version(void);
 const char *dge_status_string(int status);
 
 /* Bytes of device workspace the given operation needs for this geometry.
- * DGE_OP_SCORE: per-row softmax partials of dge_score (sized for w + k scoring rows).
+ * DGE_OP_SCORE: per-row softmax partials of dge_score (the largest of the three row modes),
+ *               and for launches of few scoring rows over a large K (e.g. draft rows over 32
+ *               layers) up to 256 MiB for their logits; a smaller workspace that holds the
+ *               partials is accepted and gives the same scores with a second pass over K.
  * DGE_OP_SELECT: radix keys of dge_select_topb.
  * DGE_OP_H2O: partial column sums of dge_h2o_colsum, plus the per-row log-sum-exp
  *             for calls where the caller supplies none.

@@ -50,6 +50,14 @@ dge_status_t check_tail(const dge_geom_t* g, int32_t n_tail) {
   return DGE_OK;
 }
 
+// The part of a score workspace that holds kept logits, nullptr when it has no room for them
+// (the scores then take a second pass over K, with the same result).
+float* logits_of(const dge_geom_t& g, const ScorePlan& p, void* ws, size_t ws_bytes) {
+  const size_t base = dge::score_workspace_bytes(g, p);
+  if (p.logit_heads == 0 || ws_bytes < base + dge::score_logit_bytes(g, p)) return nullptr;
+  return reinterpret_cast<float*>(static_cast<char*>(ws) + base);
+}
+
 dge_status_t hip_status(hipError_t e) { return e == hipSuccess ? DGE_OK : DGE_ERR_HIP; }
 
 // Scratch of dge_score_noalloc: one fixed array per GPU, held until the process ends.  In
@@ -111,11 +119,10 @@ dge_status_t dge_workspace_size(const dge_geom_t* geom, int32_t op, size_t* byte
   if (st != DGE_OK) return st;
   switch (op) {
     case DGE_OP_SCORE: {
-      // the largest scoring-row set (window + draft) bounds every mode
-      const ScorePlan p = dge::plan_score(*geom, DGE_ROWS_WINDOW_DRAFT);
-      size_t best = dge::score_workspace_bytes(*geom, p);
-      for (int m = 1; m <= 2; ++m) {
-        const size_t s = dge::score_workspace_bytes(*geom, dge::plan_score(*geom, m));
+      size_t best = 0;
+      for (int m = DGE_ROWS_WINDOW_DRAFT; m <= DGE_ROWS_WINDOW; ++m) {
+        const ScorePlan p = dge::plan_score(*geom, m);
+        const size_t s = dge::score_workspace_bytes(*geom, p) + dge::score_logit_bytes(*geom, p);
         best = s > best ? s : best;
       }
       *bytes = best;
@@ -134,7 +141,8 @@ dge_status_t dge_score(const dge_geom_t* geom, int32_t rows, const void* q, cons
   const ScorePlan p = dge::plan_score(*geom, rows);
   if (ws == nullptr || !aligned16(ws) || ws_bytes < dge::score_workspace_bytes(*geom, p))
     return DGE_ERR_WORKSPACE;
-  return hip_status(dge::launch_score(*geom, p, q, k, nullptr, raw, ws, stream));
+  return hip_status(dge::launch_score(*geom, p, q, k, nullptr, raw, ws, logits_of(*geom, p, ws, ws_bytes),
+                                      stream));
 }
 
 dge_status_t dge_score_with_lse(const dge_geom_t* geom, int32_t rows, const void* q,
@@ -146,7 +154,8 @@ dge_status_t dge_score_with_lse(const dge_geom_t* geom, int32_t rows, const void
   const ScorePlan p = dge::plan_score(*geom, rows);
   if (ws == nullptr || !aligned16(ws) || ws_bytes < dge::score_workspace_bytes(*geom, p))
     return DGE_ERR_WORKSPACE;
-  return hip_status(dge::launch_score(*geom, p, q, k, nullptr, raw, ws, stream, row_lse));
+  return hip_status(dge::launch_score(*geom, p, q, k, nullptr, raw, ws, logits_of(*geom, p, ws, ws_bytes),
+                                      stream, row_lse));
 }
 
 dge_status_t dge_score_noalloc(const dge_geom_t* geom, int32_t rows, const void* q,
@@ -157,7 +166,7 @@ dge_status_t dge_score_noalloc(const dge_geom_t* geom, int32_t rows, const void*
   if (dge::score_workspace_bytes(*geom, p) > DGE_NOALLOC_SCRATCH_BYTES) return DGE_ERR_WORKSPACE;
   void* ws = nullptr;
   if ((st = scratch_of_current_device(&ws)) != DGE_OK) return st;
-  return hip_status(dge::launch_score(*geom, p, q, k, nullptr, raw, ws, stream));
+  return hip_status(dge::launch_score(*geom, p, q, k, nullptr, raw, ws, nullptr, stream));
 }
 
 dge_status_t dge_score_lse(const dge_geom_t* geom, int32_t rows, const void* q, const void* k,
@@ -174,7 +183,7 @@ dge_status_t dge_score_lse(const dge_geom_t* geom, int32_t rows, const void* q, 
   const ScorePlan p = dge::plan_score(*geom, rows);
   if (p.n_rows <= 0) return DGE_ERR_INVALID;
   if (p.groups != 1) return DGE_ERR_UNSUPPORTED;
-  return hip_status(dge::launch_score(*geom, p, q, k, row_lse, raw, nullptr, stream));
+  return hip_status(dge::launch_score(*geom, p, q, k, row_lse, raw, nullptr, nullptr, stream));
 }
 
 dge_status_t dge_select_topb(const dge_geom_t* geom, const float* scores, int32_t pool_kernel,

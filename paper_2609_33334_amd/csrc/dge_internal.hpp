@@ -25,6 +25,7 @@ struct ScorePlan {
   int c_tiles;         // the same three for the colsum pass, which only needs the merged
   int c_chunk_keys;    // row normalisers and may split the keys differently
   int c_n_chunks;
+  int logit_heads;     // KV heads whose logits are kept at a time (0: the logits are not kept)
 };
 
 struct SeqOffsets;
@@ -32,11 +33,12 @@ SeqOffsets seq_offsets(const dge_geom_t& g);
 int64_t total_rows(const dge_geom_t& g);
 int64_t max_seq_rows(const dge_geom_t& g);
 ScorePlan plan_score(const dge_geom_t& g, int rows_mode);
-size_t score_workspace_bytes(const dge_geom_t& g, const ScorePlan& p);
+size_t score_workspace_bytes(const dge_geom_t& g, const ScorePlan& p);   // a multiple of 16
+size_t score_logit_bytes(const dge_geom_t& g, const ScorePlan& p);       // the kept logits, after it
 
 hipError_t launch_score(const dge_geom_t& g, const ScorePlan& p, const void* q, const void* k,
-                        const float* row_lse, float* raw, void* ws, hipStream_t stream,
-                        float* lse_out = nullptr);
+                        const float* row_lse, float* raw, void* ws, float* logits,
+                        hipStream_t stream, float* lse_out = nullptr);
 
 size_t select_workspace_bytes(const dge_geom_t& g);
 hipError_t launch_select_topb(const dge_geom_t& g, const float* scores, int pool_kernel,

@@ -53,6 +53,7 @@
 // a private ring, with no barrier in the loop (score_stats_wave_kernel,
 // score_colsum_wave_kernel): under the passes' arithmetic on random operands the
 // per-tile barrier of the shared ring slows the K stream.
+#include <algorithm>
 #include <type_traits>
 
 #include "dge_device.hpp"
@@ -72,6 +73,8 @@ struct ScoreArgs {
   float* rowc;       // [batch][H_kv][M_pad]  log2 of each row's softmax normaliser
   const float* lse_in;      // optional [H_q][batch * n_rows] natural-log row LSE
   float* lse_out;           // optional output: the merged row LSE, natural log, same layout
+  float* logits;            // optional [H_kv][M][logit_stride]: the stats pass keeps its logits
+  int64_t logit_stride;     // floats between the rows of logits
   SeqOffsets offs;
   int64_t kv_head_stride;   // elements
   int64_t q_head_stride;    // elements between query heads = batch * n_rows * D
@@ -325,6 +328,12 @@ __device__ __forceinline__ void stats_rows_init(const ScoreArgs& a, int tile0, i
   }
 }
 
+// First float of sequence b (cached rows from s0) within a row of the kept logits: a multiple
+// of 4, with room for the 4-key group that reaches past each sequence's end.
+__host__ __device__ __forceinline__ int64_t logit_start(int64_t s0, int b) {
+  return ((s0 + 3) & ~(int64_t)3) + 8 * (int64_t)b;
+}
+
 // Logit of key j for a row at position pos, -inf where it is masked.  MASK bodies run
 // only on tiles that reach past the sequence or past the first scoring position.
 __device__ __forceinline__ float stats_mask(float x, int j, bool live, int pos, int N) {
@@ -336,7 +345,7 @@ template <typename T, int D, int FT, int RT, bool MASK>
 __device__ __forceinline__ void stats_tile_body(const ScoreArgs& a, const char* lds, int j0, int N,
                                                 int wv, int c16, int g16,
                                                 const u32x4_t (&qf)[FT + RT][RowChunks<T, D>::kSteps],
-                                                StatsRows<FT + RT>& st) {
+                                                StatsRows<FT + RT>& st, float* lrow) {
   constexpr int NS = RowChunks<T, D>::kSteps;
   constexpr int SG = sub_group<FT>();
   f32x4_t accr[RT > 0 ? RT : 1];
@@ -392,6 +401,11 @@ __device__ __forceinline__ void stats_tile_body(const ScoreArgs& a, const char* 
         if constexpr (MASK)
           x[r][t] = stats_mask(x[r][t], j0 + wv * 16 + 4 * g16 + t, st.live[FT + r], st.pos[FT + r], N);
       }
+    if constexpr (FT == 0 && RT == 1) {    // the logits themselves, where the launch keeps them
+      const int j = j0 + wv * 16 + 4 * g16;
+      if (lrow != nullptr && (!MASK || j < N))
+        *reinterpret_cast<float4*>(lrow + j) = make_float4(x[0][0], x[0][1], x[0][2], x[0][3]);
+    }
     rebase_lse_update<RT, 4>(x, a.scale_log2, st.mref + FT, st.srow + FT);
   }
 }
@@ -400,11 +414,11 @@ template <typename T, int D, int FT, int RT>
 __device__ __forceinline__ void stats_tile(const ScoreArgs& a, const char* lds, int j0, int N,
                                            int p0, int wv, int c16, int g16,
                                            const u32x4_t (&qf)[FT + RT][RowChunks<T, D>::kSteps],
-                                           StatsRows<FT + RT>& st) {
+                                           StatsRows<FT + RT>& st, float* lrow) {
   // masking only where the tile reaches past the first scoring position: padding rows
   // (not live) elsewhere accumulate harmless sums that are never stored
-  if (j0 + KT - 1 > p0) stats_tile_body<T, D, FT, RT, true>(a, lds, j0, N, wv, c16, g16, qf, st);
-  else stats_tile_body<T, D, FT, RT, false>(a, lds, j0, N, wv, c16, g16, qf, st);
+  if (j0 + KT - 1 > p0) stats_tile_body<T, D, FT, RT, true>(a, lds, j0, N, wv, c16, g16, qf, st, lrow);
+  else stats_tile_body<T, D, FT, RT, false>(a, lds, j0, N, wv, c16, g16, qf, st, lrow);
 }
 
 // Merge the four lane groups that hold the same row: every lane ends with its row's
@@ -573,9 +587,14 @@ __global__ __launch_bounds__(kThreads, (stats_waves<T, D, FT, RT>())) void score
     q_fence(qf);                           // landed with the first tile
     StatsRows<NQ> st;
     stats_rows_init<FT, NQ>(a, tile0, wv, c16, p0, st);
+    float* lrow = nullptr;                 // this lane's row of the kept logits
+    if constexpr (FT == 0 && RT == 1) {
+      if (a.logits != nullptr && c16 < a.M)
+        lrow = a.logits + ((int64_t)h * a.M + c16) * a.logit_stride + logit_start(s0, b);
+    }
     ktile_stream<T, D, S>(kb, c0, ntiles, N, ldsbuf, kcp,
                        [&](const char* lds, int j0, int) {
-                         stats_tile<T, D, FT, RT>(a, lds, j0, N, p0, wv, c16, g16, qf, st);
+                         stats_tile<T, D, FT, RT>(a, lds, j0, N, p0, wv, c16, g16, qf, st, lrow);
                        });
     stats_rows_merge<NQ>(st);
 #pragma unroll
@@ -1053,6 +1072,56 @@ __global__ __launch_bounds__(kThreads, 2) void score_colsum_wave_kernel(ScoreArg
   asm_wait_vmcnt<0>();                         // no copy still writes into the ring
 }
 
+// Column sums from the logits the stats pass kept (at most 16 query rows per KV head): a
+// thread per key and kLogitKeys keys apart, every row's logits read coalesced, the terms added
+// in the order of the colsum kernel (4 rows, then rows 0-3 + 8-11 and 4-7 + 12-15), so both
+// routes give the same bits.
+//   Why: with few rows both passes are bound by streaming K, and the logits are a fraction of
+// it (8 rows: 32 bytes a key against 256).  Reading K once, writing and reading the logits
+// moves rowBytes + 8 M bytes a key instead of 2 rowBytes (bounds: plan_score).
+constexpr int kLogitKeys = 4;
+__global__ __launch_bounds__(kThreads) void score_logit_colsum_kernel(ScoreArgs a) {
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int64_t s0 = a.offs[b];
+  const int N = (int)(a.offs[b + 1] - s0);
+  const int j0 = (int)blockIdx.x * kThreads * kLogitKeys + (int)threadIdx.x;
+  if ((int)blockIdx.x * kThreads * kLogitKeys >= N) return;
+  const float* lg = a.logits + (int64_t)h * a.M * a.logit_stride + logit_start(s0, b);
+  const float* rowc = a.rowc + (int64_t)(b * a.n_kv_heads + h) * a.M_pad;
+  float* out = a.raw + (int64_t)h * a.total_rows + s0;
+  float part[kLogitKeys][4];
+#pragma unroll
+  for (int u = 0; u < kLogitKeys; ++u)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) part[u][g] = 0.0f;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    if (4 * g >= a.M) break;               // uniform
+    float x[kLogitKeys][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int u = 0; u < kLogitKeys; ++u) {
+        const int j = j0 + u * kThreads;
+        x[u][t] = (4 * g + t < a.M && j < N) ? lg[(4 * g + t) * a.logit_stride + j] : -INFINITY;
+      }
+    float e[kLogitKeys][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float c = rowc[min(4 * g + t, a.M - 1)];
+#pragma unroll
+      for (int u = 0; u < kLogitKeys; ++u) e[u][t] = fast_exp2(fmaf(x[u][t], a.scale_log2, -c));
+    }
+#pragma unroll
+    for (int u = 0; u < kLogitKeys; ++u) part[u][g] = (e[u][0] + e[u][1]) + (e[u][2] + e[u][3]);
+  }
+#pragma unroll
+  for (int u = 0; u < kLogitKeys; ++u) {
+    const int j = j0 + u * kThreads;
+    if (j < N) out[j] = ((part[u][0] + part[u][2]) + (part[u][1] + part[u][3])) * a.inv_G;
+  }
+}
+
 template <typename T, int D, int FT, int RT>
 hipError_t launch_typed(const ScoreArgs& a, const dge_geom_t& g, hipStream_t st) {
   const dim3 grid(xcd_grid(a.n_chunks * g.n_kv_heads * g.batch));
@@ -1072,6 +1141,15 @@ hipError_t launch_typed(const ScoreArgs& a, const dge_geom_t& g, hipStream_t st)
     else
       hipLaunchKernelGGL(score_reduce_chunks_kernel, dim3(a.M_pad / 4, g.n_kv_heads, g.batch),
                          dim3(256), 0, st, a);
+    if constexpr (FT == 0 && RT == 1) {
+      if (a.logits != nullptr) {
+        constexpr int kKeys = kThreads * kLogitKeys;
+        hipLaunchKernelGGL(score_logit_colsum_kernel,
+                           dim3((unsigned)((max_seq_rows(g) + kKeys - 1) / kKeys), g.n_kv_heads, g.batch),
+                           dim3(kThreads), 0, st, a);
+        return hipGetLastError();
+      }
+    }
   }
   // the colsum pass with its own split of the keys (it reads only the merged normalisers)
   ScoreArgs ac = a;
@@ -1145,6 +1223,12 @@ int64_t max_seq_rows(const dge_geom_t& g) {
   return m;
 }
 
+namespace {
+constexpr int64_t kLogitBytes = (int64_t)256 << 20;
+constexpr int64_t kLogitMinK = (int64_t)128 << 20;
+int64_t logit_row_floats(const dge_geom_t& g) { return logit_start(total_rows(g), g.batch); }
+}  // namespace
+
 ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
   ScorePlan p{};
   switch (rows_mode) {
@@ -1206,7 +1290,29 @@ ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
   p.c_chunk_keys = KT * citers;
   p.c_n_chunks = (int)((nmax + p.c_chunk_keys - 1) / p.c_chunk_keys);
   if (p.c_n_chunks < 1) p.c_n_chunks = 1;
+  // Few query rows (one row tile): the stats pass keeps its logits, for as many heads at a
+  // time as kLogitBytes hold, and the column sums come from them instead of a second pass
+  // over K (see score_logit_colsum_kernel), where that moves at most 3/4 of the bytes
+  // (8 M <= half a row of K) and K is at least kLogitMinK: a smaller K is found in the 256 MB
+  // Infinity Cache by the second pass.  Measured, two passes against kept logits, 8 rows of
+  // bf16 d = 128: 34 and 101 MB of K 16 and 39 us either way, 134 MB 52 -> 43, 268 MB 97 -> 76,
+  // 1.07 GB 386 -> 275 (4.9 TB/s of reads and writes, what a device copy reaches), 13.2 GB
+  // 4.7 -> 3.7 ms; 16 rows, 268 MB 106 either way, 1.07 GB 396 -> 342 us.  Buffers of 32, 64
+  // and 128 MB for the 1.07 GB took 375, 297 and 290 us (each head range ends in a partial
+  // round of workgroups), one range 275.
+  const int64_t row_bytes = (int64_t)g.head_dim * (g.dtype == DGE_BF16 ? 2 : 4);
+  const int64_t head_bytes = p.M * logit_row_floats(g) * (int64_t)sizeof(float);
+  if (p.M > 0 && p.n_tiles == 1 && 16 * p.M <= row_bytes && head_bytes <= kLogitBytes &&
+      g.n_kv_heads * total_rows(g) * row_bytes >= kLogitMinK) {
+    const int64_t fit = kLogitBytes / head_bytes;
+    const int64_t rounds = (g.n_kv_heads + fit - 1) / fit;
+    p.logit_heads = (int)((g.n_kv_heads + rounds - 1) / rounds);
+  }
   return p;
+}
+
+size_t score_logit_bytes(const dge_geom_t& g, const ScorePlan& p) {
+  return (size_t)p.logit_heads * p.M * logit_row_floats(g) * sizeof(float);
 }
 
 size_t score_workspace_bytes(const dge_geom_t& g, const ScorePlan& p) {
@@ -1215,7 +1321,7 @@ size_t score_workspace_bytes(const dge_geom_t& g, const ScorePlan& p) {
 }
 
 hipError_t launch_score(const dge_geom_t& g, const ScorePlan& p, const void* q, const void* k,
-                        const float* row_lse, float* raw, void* ws, hipStream_t st,
+                        const float* row_lse, float* raw, void* ws, float* logits, hipStream_t st,
                         float* lse_out) {
   ScoreArgs a{};
   a.lse_in = row_lse;
@@ -1247,12 +1353,32 @@ hipError_t launch_score(const dge_geom_t& g, const ScorePlan& p, const void* q, 
   a.c_n_chunks = p.c_n_chunks;
   a.scale_log2 = kLog2e / sqrtf((float)g.head_dim);
   a.inv_G = 1.0f / (float)a.G;
-  if (g.dtype == DGE_BF16) {
-    return g.head_dim == 128 ? launch_split<bf16_t, 128>(a, g, p.ft, p.rt, st)
-                             : launch_split<bf16_t, 64>(a, g, p.ft, p.rt, st);
+  auto launch = [&](const ScoreArgs& x, const dge_geom_t& gx) {
+    if (g.dtype == DGE_BF16)
+      return g.head_dim == 128 ? launch_split<bf16_t, 128>(x, gx, p.ft, p.rt, st)
+                               : launch_split<bf16_t, 64>(x, gx, p.ft, p.rt, st);
+    return g.head_dim == 128 ? launch_split<float, 128>(x, gx, p.ft, p.rt, st)
+                             : launch_split<float, 64>(x, gx, p.ft, p.rt, st);
+  };
+  if (logits == nullptr || p.logit_heads == 0) return launch(a, g);
+  // head range by head range through one logits buffer, all with the plan of the whole
+  a.logits = logits;
+  a.logit_stride = logit_row_floats(g);
+  const int64_t elt = g.dtype == DGE_BF16 ? 2 : 4;
+  for (int h0 = 0; h0 < g.n_kv_heads; h0 += p.logit_heads) {
+    dge_geom_t gx = g;
+    gx.n_kv_heads = std::min(p.logit_heads, g.n_kv_heads - h0);
+    gx.n_q_heads = gx.n_kv_heads * a.G;
+    ScoreArgs x = a;
+    x.n_kv_heads = gx.n_kv_heads;
+    x.q = static_cast<const char*>(q) + (int64_t)h0 * a.G * a.q_head_stride * elt;
+    x.k = static_cast<const char*>(k) + h0 * g.kv_head_stride * elt;
+    x.raw = raw + h0 * a.total_rows;
+    if (lse_out != nullptr) x.lse_out = lse_out + (int64_t)h0 * a.G * g.batch * p.n_rows;
+    const hipError_t e = launch(x, gx);
+    if (e != hipSuccess) return e;
   }
-  return g.head_dim == 128 ? launch_split<float, 128>(a, g, p.ft, p.rt, st)
-                           : launch_split<float, 64>(a, g, p.ft, p.rt, st);
+  return hipSuccess;
 }
 
 }  // namespace dge

@@ -344,6 +344,53 @@ def test_score_lse_single_pass(case):
     check_scores(raw.cpu().numpy(), want, f"score_lse {case}")
 
 
+# (dtype, d, H_q, H_kv, k, prompt lens): at most 16 draft rows per KV head over at least 128 MiB
+# of K: odd and ragged lengths, a sequence of k + 1 rows, 1 / 3 / 6 / 8 / 16 rows; the last
+# case needs two ranges of heads (more than 256 MiB of logits)
+KEPT_LOGIT_CASES = [
+    ("bf16", 128, 512, 256, 3, (1501, 702, 1)),
+    ("bf16", 128, 256, 256, 1, (2063,)),
+    ("bf16", 64, 512, 256, 4, (4099, 30)),
+    ("f32", 64, 256, 256, 3, (1030, 1029)),
+    ("f32", 128, 128, 64, 8, (4098,)),
+    ("bf16", 128, 1024, 512, 8, (8321,)),
+]
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv,k,lens", KEPT_LOGIT_CASES)
+def test_score_few_rows_kept_logits_vs_two_passes_and_oracle(dtype, d, hq, hkv, k, lens):
+    """Scoring by few rows over a large K keeps the logits in the workspace; a workspace
+    without room for them takes the second pass over K.  Same bits, and two heads against
+    the oracle."""
+    _log(f"kept logits {dtype} d={d} heads={hq}/{hkv} k={k} lens={lens}")
+    g = dge.Geometry(hq, hkv, d, 0, k, [n + k for n in lens],
+                     dtype=dge.DGE_BF16 if dtype == "bf16" else dge.DGE_F32, device=DEV)
+    assert g.total_rows * hkv * d * (2 if dtype == "bf16" else 4) >= 128 << 20
+    full = dge.workspace_size(g, dge.OP_SCORE)
+    logits = 4 * hkv * (hq // hkv) * k * g.total_rows
+    assert full > min(logits, 128 << 20)   # more than 256 MiB: equal ranges, each above half of it
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(17 + k)
+    q = torch.randn(hq, len(lens) * k, d, generator=gen, device=DEV).to(g.elt_dtype)
+    key = torch.empty(hkv, g.total_rows, d, dtype=g.elt_dtype, device=DEV)
+    for h in range(0, hkv, 64):
+        key[h:h + 64] = torch.randn(key[h:h + 64].shape, generator=gen, device=DEV)
+    raw, lse = dge.score_with_lse(g, dge.ROWS_DRAFT, q, key)
+    small = torch.empty(4 << 20, dtype=torch.uint8, device=DEV)
+    raw2, lse2 = dge.score_with_lse(g, dge.ROWS_DRAFT, q, key, ws=small)
+    raw3 = dge.score_noalloc(g, dge.ROWS_DRAFT, q, key)
+    torch.cuda.synchronize()
+    assert torch.equal(raw.view(torch.int32), raw2.view(torch.int32))
+    assert torch.equal(raw.view(torch.int32), raw3.view(torch.int32))
+    assert torch.equal(lse.view(torch.int32), lse2.view(torch.int32))
+    G = hq // hkv
+    for h in (0, hkv - 1):
+        want = oracle.window_scores(q[h * G:(h + 1) * G].float().cpu().numpy(),
+                                    key[h:h + 1].float().cpu().numpy(), g.offsets_host, G, 1, 0, k,
+                                    oracle.ROWS_DRAFT)
+        check_scores(raw[h:h + 1].cpu().numpy(), want, f"head {h}")
+
+
 def test_score_deterministic():
     wl = di.small_variant("c2", [2000, 900])
     x = di.make_layer(wl, with_v=False)
