@@ -10,6 +10,7 @@ Tolerances (written here, derived in the design notes):
   1e-3 is dropped, and the counts agree;
 * compaction: byte-exact given the GPU's own indices.
 """
+import dataclasses
 import math
 import sys
 
@@ -614,6 +615,29 @@ def _wide_logit_layer(kind, lens):
         qsb[:, b * nr:(b + 1) * nr] = x.q_all_bits[:, s0 + N - nr:s0 + N]
     x.q, x.q_bits = qs, qsb
     return wl, x
+
+
+@pytest.mark.parametrize("supply_lse", [False, True])
+@pytest.mark.parametrize("n_q_heads", [2, 4, 8])
+@pytest.mark.parametrize("lens", [(3, 15, 17), (127, 129, 641), (513, 128, 1025)])
+def test_h2o_group_sizes_and_tile_edges(lens, n_q_heads, supply_lse):
+    """One to four query heads per KV head, over the edges of the 16-key subtiles, 64-row
+    and 128-row blocks and 512-row segments, in ragged batches (short sequences leave some
+    wavefronts of a block without a subtile)."""
+    _log(f"h2o edges lens={lens} hq={n_q_heads} supply_lse={supply_lse}")
+    wl = dataclasses.replace(di.small_variant("c5", [n - 2 for n in lens]), n_q_heads=n_q_heads,
+                             n_kv_heads=2)
+    assert wl.cached_lens == tuple(lens)
+    x = di.make_layer(wl, with_v=False)
+    g = geom_of(wl)
+    lse = None
+    if supply_lse:
+        ref = oracle.h2o_row_lse(x.q_all, x.k, wl.kv_offsets, wl.n_q_heads, wl.n_kv_heads)
+        lse = torch.from_numpy(np.ascontiguousarray(ref, dtype=np.float32)).to(DEV)
+    col = dge.h2o_colsum(g, to_dev(x.q_all_bits, "bf16"), to_dev(x.k_bits, "bf16"), lse=lse)
+    torch.cuda.synchronize()
+    want = oracle.h2o_colsum(x.q_all, x.k, wl.kv_offsets, wl.n_q_heads, wl.n_kv_heads)
+    check_scores(col.cpu().numpy(), want, "h2o_edges")
 
 
 @pytest.mark.parametrize("kind", ["ramp", "step"])
