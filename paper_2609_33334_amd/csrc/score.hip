@@ -86,6 +86,21 @@ struct ScoreArgs {
   float inv_G;
 };
 
+// Units are numbered (chunk, sequence, KV head), the head slowest: each XCD's contiguous range
+// then holds heads of every sequence and not the long or the short sequences of a ragged
+// batch (three sequences of 5.9K to 10.4K tokens, 16 layers, row log-sum-exp given: 219 ->
+// 196 us).
+//
+// Keys per chunk of a sequence of N rows: it has as many chunks as walks of chunk_keys cover
+// it, and its 64-key tiles are spread evenly over them (the last of them is never empty: with
+// n = ceil(t / w), ceil(t / ceil(t / n)) is n again).  The host has done so for the longest
+// sequence.
+__device__ __forceinline__ int chunk_step(const ScoreArgs& a, int N) {
+  if (a.batch == 1) return a.chunk_keys;
+  const int tiles = (N + KT - 1) / KT, n = (tiles + a.iters - 1) / a.iters;
+  return n > 0 ? (tiles + n - 1) / n * KT : a.chunk_keys;
+}
+
 template <typename T, int D>
 struct KTile {
   static constexpr int kRowBytes = D * Elem<T>::kBytes;
@@ -286,17 +301,19 @@ template <typename T, int D, int FT, int RT>
 constexpr int stats_waves() { return score_waves<T, D, FT, RT>(); }
 // The colsum pass at Llama-3-8B-like row counts (bf16, d = 128, at most two own and one
 // shared tile per wavefront) also fits three wavefronts per SIMD (<= 168 registers) with a
-// 3-stage ring; the stats pass at three spills.  Three are faster on launches of many
-// rounds of workgroups (32 layers of a batch of 8 sequences of 16K-32K tokens: colsum
-// 3.2 -> 2.9 ms) and slower on launches of one or two rounds (32 layers of one 16K
-// sequence, 1280 workgroups: 2-4%, the last round then leaving compute units idle), so
-// the launch picks the instance by its workgroup count (kColsumThreeWaveUnits).
+// 3-stage ring; the stats pass at three spills.  Three are as fast as two on the shortest
+// walks (one layer of 4096 and 16000 tokens, 34 rows: 20.6 against 20.9 and 29.2 against
+// 29.7 us for the three launches) and faster on longer ones (4 layers, four sequences of 8K
+// to 15K tokens: 174 -> 162 us; 12 layers, two of 6K to 9K: 172 -> 161 us).  With fewer than
+// four row tiles (draft rows) a walk is bound by its copies and two wavefronts with the
+// 4-stage ring are faster (8 layers of 8000 tokens, 32 rows: 47.0 against 49.7 us) up to
+// kColsumThreeWaveUnits workgroups.
+constexpr int kColsumThreeWaveUnits = 4096;
 template <typename T, int D, int FT, int RT>
-constexpr int colsum_max_waves() {
+constexpr int colsum_waves() {
   return std::is_same<T, bf16_t>::value && D == 128 && FT <= 2 && RT <= 1
              ? 3 : score_waves<T, D, FT, RT>();
 }
-constexpr int kColsumThreeWaveUnits = 4096;
 
 // Depth of the K ring of a kernel compiled for W wavefronts per SIMD (W workgroups per
 // compute unit share its 160 KB of LDS): 4 stages of 16 KB (3 tiles in flight) for up
@@ -558,16 +575,16 @@ __global__ __launch_bounds__(kThreads, (stats_waves<T, D, FT, RT>())) void score
   const int units = a.n_chunks * a.n_kv_heads * a.batch;
   const int unit = xcd_unit(units);
   if (unit >= units) return;
-  const int chunk = unit % a.n_chunks, h = (unit / a.n_chunks) % a.n_kv_heads,
-            b = unit / (a.n_chunks * a.n_kv_heads);
+  const int chunk = unit % a.n_chunks, b = (unit / a.n_chunks) % a.batch,
+            h = unit / (a.n_chunks * a.batch);
   const int64_t s0 = a.offs[b];
   const int N = (int)(a.offs[b + 1] - s0);
-  const int c0 = chunk * a.chunk_keys;
+  const int step = chunk_step(a, N), c0 = chunk * step;
   if (c0 >= N) return;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int g16 = lane >> 4, c16 = lane & 15;
   const int p0 = N - a.p0_from_end;
-  const int c1 = min(N, c0 + a.chunk_keys);
+  const int c1 = min(N, c0 + step);
   const int ntiles = (c1 - c0 + KT - 1) / KT;
   const char* kb = reinterpret_cast<const char*>(a.k) +
                    ((int64_t)h * a.kv_head_stride + s0 * D) * Elem<T>::kBytes;
@@ -709,17 +726,17 @@ __global__ __launch_bounds__(kThreads, 2) void score_stats_wave_kernel(ScoreArgs
   const int units = a.n_chunks * a.n_kv_heads * a.batch;
   const int unit = xcd_unit(units);
   if (unit >= units) return;
-  const int chunk = unit % a.n_chunks, h = (unit / a.n_chunks) % a.n_kv_heads,
-            b = unit / (a.n_chunks * a.n_kv_heads);
+  const int chunk = unit % a.n_chunks, b = (unit / a.n_chunks) % a.batch,
+            h = unit / (a.n_chunks * a.batch);
   const int64_t s0 = a.offs[b];
   const int N = (int)(a.offs[b + 1] - s0);
-  const int c0 = chunk * a.chunk_keys;
+  const int step = chunk_step(a, N), c0 = chunk * step;
   if (c0 >= N) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform for the copies
   const int g16 = lane >> 4, c16 = lane & 15;
   const int p0 = N - a.p0_from_end;
-  const int c1 = min(N, c0 + a.chunk_keys);
+  const int c1 = min(N, c0 + step);
   const int nsub = (c1 - c0 + kSubKeys - 1) / kSubKeys;
   const int per = (nsub + 3) / 4;                        // subtiles per wavefront
   const int w0 = c0 + wv * per * kSubKeys;               // first key of this wavefront's run
@@ -889,16 +906,16 @@ __global__ __launch_bounds__(kThreads, W) void score_colsum_kernel(ScoreArgs a) 
   const int units = a.n_chunks * a.n_kv_heads * a.batch;
   const int unit = xcd_unit(units);
   if (unit >= units) return;
-  const int chunk = unit % a.n_chunks, h = (unit / a.n_chunks) % a.n_kv_heads,
-            b = unit / (a.n_chunks * a.n_kv_heads);
+  const int chunk = unit % a.n_chunks, b = (unit / a.n_chunks) % a.batch,
+            h = unit / (a.n_chunks * a.batch);
   const int64_t s0 = a.offs[b];
   const int N = (int)(a.offs[b + 1] - s0);
-  const int c0 = chunk * a.chunk_keys;
+  const int step = chunk_step(a, N), c0 = chunk * step;
   if (c0 >= N) return;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int g16 = lane >> 4, c16 = lane & 15;
   const int p0 = N - a.p0_from_end;
-  const int c1 = min(N, c0 + a.chunk_keys);
+  const int c1 = min(N, c0 + step);
   const int ntiles = (c1 - c0 + KT - 1) / KT;
   const char* kb = reinterpret_cast<const char*>(a.k) +
                    ((int64_t)h * a.kv_head_stride + s0 * D) * Elem<T>::kBytes;
@@ -979,17 +996,17 @@ __global__ __launch_bounds__(kThreads, 2) void score_colsum_wave_kernel(ScoreArg
   const int units = a.n_chunks * a.n_kv_heads * a.batch;
   const int unit = xcd_unit(units);
   if (unit >= units) return;
-  const int chunk = unit % a.n_chunks, h = (unit / a.n_chunks) % a.n_kv_heads,
-            b = unit / (a.n_chunks * a.n_kv_heads);
+  const int chunk = unit % a.n_chunks, b = (unit / a.n_chunks) % a.batch,
+            h = unit / (a.n_chunks * a.batch);
   const int64_t s0 = a.offs[b];
   const int N = (int)(a.offs[b + 1] - s0);
-  const int c0 = chunk * a.chunk_keys;
+  const int step = chunk_step(a, N), c0 = chunk * step;
   if (c0 >= N) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g16 = lane >> 4, c16 = lane & 15;
   const int p0 = N - a.p0_from_end;
-  const int c1 = min(N, c0 + a.chunk_keys);
+  const int c1 = min(N, c0 + step);
   const int nsub = (c1 - c0 + kSubKeys - 1) / kSubKeys;
   const int per = (nsub + 3) / 4;
   const int w0 = c0 + wv * per * kSubKeys;
@@ -1158,7 +1175,6 @@ hipError_t launch_typed(const ScoreArgs& a, const dge_geom_t& g, hipStream_t st)
   ac.n_chunks = a.c_n_chunks;
   const int cunits = ac.n_chunks * g.n_kv_heads * g.batch;
   const dim3 gridc(xcd_grid(cunits));
-  constexpr int W2 = score_waves<T, D, FT, RT>(), W3 = colsum_max_waves<T, D, FT, RT>();
   constexpr int NQC = 4 * FT + RT;
   if constexpr (std::is_same<T, bf16_t>::value && D == 128 && (NQC == 8 || NQC == 9)) {
     if (ac.groups == 1 && ac.n_tiles == NQC && ac.iters >= kWaveStatsMinTiles) {
@@ -1166,10 +1182,14 @@ hipError_t launch_typed(const ScoreArgs& a, const dge_geom_t& g, hipStream_t st)
       return hipGetLastError();
     }
   }
-  if (W3 != W2 && cunits >= kColsumThreeWaveUnits)
-    hipLaunchKernelGGL((score_colsum_kernel<T, D, FT, RT, W3>), gridc, dim3(kThreads), 0, st, ac);
-  else
-    hipLaunchKernelGGL((score_colsum_kernel<T, D, FT, RT, W2>), gridc, dim3(kThreads), 0, st, ac);
+  constexpr int W2 = score_waves<T, D, FT, RT>(), W3 = colsum_waves<T, D, FT, RT>();
+  if constexpr (FT == 0 && W3 != W2) {
+    if (cunits < kColsumThreeWaveUnits) {
+      hipLaunchKernelGGL((score_colsum_kernel<T, D, FT, RT, W2>), gridc, dim3(kThreads), 0, st, ac);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((score_colsum_kernel<T, D, FT, RT, W3>), gridc, dim3(kThreads), 0, st, ac);
   return hipGetLastError();
 }
 
@@ -1278,14 +1298,49 @@ ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
     return units128 >= kLongWalkUnits ? w128 : even(64);
   };
   int iters = balanced((int)((tiles_total + 255) / 256));
+  // A launch of few rounds of workgroups (two per compute unit) leaves much of the chip idle
+  // in a partial last round, so up to two rounds the walk is the one with the least rounds x
+  // (tiles + kWalkStart), among those of at least kMinRoundWalk tiles (shorter ones are the
+  // business of the rule above); kWalkStart is what a workgroup's start costs in tiles.  Draft
+  // rows alone (fewer than four row tiles) start cheaply and gain nothing.
+  // 34 rows, 32 layers: 16384 tokens, 5 chunks (2.5 rounds) 449, 4 (two rounds) 443, 3 (1.5)
+  // 452, 2 (one round) 433 us; 3000 tokens, one chunk (half a round) 91, two (one round) 86 us.
+  constexpr int64_t kRoundUnits = 512, kWalkStart = 4, kMinRoundWalk = 24;
+  auto cost = [&](int64_t walk, int64_t* rounds) {
+    int64_t units = 0;
+    for (int b = 0; b < g.batch; ++b)
+      units += ((g.kv_offsets_host[b + 1] - g.kv_offsets_host[b] + KT - 1) / KT + walk - 1) / walk;
+    *rounds = (units * g.n_kv_heads + kRoundUnits - 1) / kRoundUnits;
+    return *rounds * (walk + kWalkStart);
+  };
+  int64_t rounds = 0, best = cost(iters, &rounds);
+  for (int64_t chunks = 1; p.n_tiles >= 4 && (seq_tiles + chunks - 1) / chunks >= kMinRoundWalk; ++chunks) {
+    const int64_t walk = (seq_tiles + chunks - 1) / chunks, c = cost(walk, &rounds);
+    // more chunks than the rule above has only while their partials stay small (4 MiB), so
+    // that a call which fits the fixed scratch keeps fitting it
+    const bool room = walk >= iters || chunks * g.n_kv_heads * g.batch * p.M_pad * 4 <= (4 << 20);
+    if (rounds > 2) break;
+    if (c < best && room) { best = c; iters = (int)walk; }
+  }
   p.tiles_per_wave = iters;
   p.chunk_keys = KT * iters;
   p.n_chunks = (int)((nmax + p.chunk_keys - 1) / p.chunk_keys);
   if (p.n_chunks < 1) p.n_chunks = 1;
   // the colsum pass walks about one tile per 512 of the launch (twice the workgroups of
   // the stats pass on small launches: one 4096-token layer of 8 KV heads 0.6 us faster
-  // with 2 tiles per colsum workgroup and 3 per stats workgroup than with 3 and 3)
-  const int citers = balanced((int)((tiles_total + 511) / 512));
+  // with 2 tiles per colsum workgroup and 3 per stats workgroup than with 3 and 3), and at
+  // most kColsumWalk tiles below kColsumLongTiles: there three wavefronts per SIMD on short
+  // walks beat the private streams on long ones (34 rows, 50K tiles in three ragged
+  // sequences, row log-sum-exp given: 212 us by 55 tiles, 179 by 12, 183 by 24; 4 layers of
+  // four sequences of 8K to 15K tokens 178 -> 156, 32 layers of three of 4K to 8K 493 -> 471
+  // us); 140K tiles take the same time either way, and at 384K long walks are 2% faster.
+  constexpr int64_t kColsumLongTiles = 128 * 1024;
+  constexpr int kColsumWalk = 24;
+  int citers = balanced((int)((tiles_total + 511) / 512));
+  if (tiles_total < kColsumLongTiles && citers > kColsumWalk) {
+    const int64_t chunks = (seq_tiles + kColsumWalk - 1) / kColsumWalk;
+    citers = (int)((seq_tiles + chunks - 1) / chunks);
+  }
   p.c_tiles = citers;
   p.c_chunk_keys = KT * citers;
   p.c_n_chunks = (int)((nmax + p.c_chunk_keys - 1) / p.c_chunk_keys);

@@ -329,6 +329,36 @@ def test_score_lse_long_walks_short_last_chunks():
         check_scores(raw[l * H:(l + 1) * H], want, f"score_lse layer copy {l}")
 
 
+@pytest.mark.parametrize("supply_lse", [False, True])
+@pytest.mark.parametrize("nl,lens", [(32, (3002,)), (12, (9002, 131, 702)), (29, (16384, 12308, 8262))])
+def test_score_stacked_layers_splits(nl, lens, supply_lse):
+    """Stacked copies of one layer at the borders of the key split: a launch that fills one
+    round of workgroups, sequences of very different lengths (each cut evenly by itself), and
+    128K tiles, where the column sums take one K stream per wavefront.  Every copy has the
+    same keys and split, so copies agree bit for bit; the first is compared with the oracle."""
+    wl = di.small_variant("c3", [n - 2 for n in lens])
+    assert tuple(wl.cached_lens) == lens
+    _log(f"score splits: {nl} layers of {lens}, supply_lse={supply_lse}")
+    x = di.make_layer(wl, layer=2, with_v=False)
+    g = dge.Geometry(wl.n_q_heads * nl, wl.n_kv_heads * nl, wl.head_dim, wl.window, wl.k_draft,
+                     wl.cached_lens, device=DEV)
+    q = to_dev(x.q_bits, "bf16").repeat(nl, 1, 1)
+    k = to_dev(x.k_bits, "bf16").repeat(nl, 1, 1)
+    if supply_lse:
+        lse = oracle.scoring_row_lse(x.q, x.k, wl.kv_offsets, wl.n_q_heads, wl.n_kv_heads, wl.window,
+                                     wl.k_draft)
+        lse_d = torch.from_numpy(lse.astype(np.float32)).to(DEV).repeat(nl, 1).contiguous()
+        raw = dge.score_lse(g, dge.ROWS_WINDOW_DRAFT, q, k, lse_d)
+    else:
+        raw = dge.score(g, dge.ROWS_WINDOW_DRAFT, q, k)
+    torch.cuda.synchronize()
+    raw = raw.view(nl, wl.n_kv_heads, -1)
+    assert torch.equal(raw, raw[:1].expand_as(raw))
+    want = oracle.window_scores(x.q, x.k, wl.kv_offsets, wl.n_q_heads, wl.n_kv_heads, wl.window,
+                                wl.k_draft)
+    check_scores(raw[0].cpu().numpy(), want, f"{nl} layers of {lens}")
+
+
 @pytest.mark.parametrize("case", ["c2", "c2_ragged", "c1"])
 def test_score_lse_single_pass(case):
     wl = {"c2": di.WORKLOADS["c2"], "c2_ragged": SCORE_CASES["c2_ragged"], "c1": di.WORKLOADS["c1"]}[case]
