@@ -427,12 +427,19 @@ __global__ __launch_bounds__(256, 2) void project_tile_kernel(ProjArgs a, int nr
 // Large tiles for many rows: 256 x 256 per workgroup, eight wavefronts, each computing 128
 // rows x 64 columns (eight row tiles; two low 16-column tiles and their partners, as
 // above).  Per 32-wide K slice a workgroup copies 32 KB into LDS for 512 products, half
-// the L2-to-LDS bytes per product of the 128 x 128 tiles; 3 stages (96 KB) leave one
+// the L2-to-LDS bytes per product of the 128 x 128 tiles; 4 stages (128 KB) leave one
 // workgroup per compute unit.  Same LDS row format and swizzle as the 128 x 128 kernel.
+// Per slice the fragment reads (96 KB, 768 cycles of LDS) and the products (1024 cycles of
+// matrix core) take nearly the same time, and all eight wavefronts meet at the slice's
+// barrier, so reads before products would serialise the two units: the next slice's reads
+// are issued one by one between this slice's products.  8194 rows, hidden 4096, 32 heads:
+// 254 us with the reads at the slice's start, 246 with all reads of the next slice ahead of
+// the products, 240 interleaved (1.15 PFLOP/s with the remainder's launch; the products
+// alone run at 1.9 here); between other calls 270 -> 259.
 // ---------------------------------------------------------------------------------------
 constexpr int kHT = 256;                        // rows and columns per workgroup
 constexpr int kHWaves = 8;
-constexpr int kHStages = 3;
+constexpr int kHStages = 4;
 constexpr int kHHalfBytes = kHT * kGBK * 2;     // A or B part of a stage: 16 KB
 constexpr int kHStageBytes = 2 * kHHalfBytes;   // 32 KB
 constexpr int kHCopies = kHStageBytes / (64 * kHWaves * 16);   // copies per thread per stage
@@ -485,14 +492,9 @@ __global__ __launch_bounds__(64 * kHWaves, 1) void project_tile256_kernel(ProjAr
   for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[i][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int t = 0; t < kHStages - 1; ++t) issue(t);
-  for (int t = 0; t < nk; ++t) {
-    asm_wait_vmcnt<(kHStages - 2) * kHCopies>();   // stage t has landed (this thread's part)
-    lds_barrier();                                 // ... everyone's; slot (t - 1) % S is free
-    issue(t + kHStages - 1);
+  // fragment reads of stage t (LDS -> registers)
+  auto frags = [&](int t, uint4 (&af)[8], uint4 (&bf)[4]) {
     const char* st = ring[t % kHStages];
-    uint4 bf[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = ct[e] * 16 + c16;
@@ -501,10 +503,36 @@ __global__ __launch_bounds__(64 * kHWaves, 1) void project_tile256_kernel(ProjAr
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int r = rh * 128 + i * 16 + c16;
-      const uint4 af = *reinterpret_cast<const uint4*>(st + r * 64 + ((g16 ^ ((r >> 1) & 3)) * 16));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][e] = mma_step(bf16_t{}, af, bf[e], acc[i][e]);
+      af[i] = *reinterpret_cast<const uint4*>(st + r * 64 + ((g16 ^ ((r >> 1) & 3)) * 16));
     }
+  };
+  // Software-pipelined as the 128 x 128 kernel: stage t + 1's fragments are read under stage
+  // t's products, from a stage that has landed for everyone at the barrier that opens step t
+#pragma unroll
+  for (int t = 0; t < kHStages - 1; ++t) issue(t);
+  asm_wait_vmcnt<(kHStages - 2) * kHCopies>();     // stage 0 has landed (this thread's part)
+  lds_barrier();                                   // ... everyone's
+  issue(kHStages - 1);
+  auto step = [&](int t, const uint4 (&af)[8], const uint4 (&bf)[4], uint4 (&an)[8], uint4 (&bn)[4]) {
+    asm_wait_vmcnt<(kHStages - 2) * kHCopies>();   // stage t + 1 has landed (this thread's part)
+    lds_barrier();                                 // ... everyone's; stage t's slot is free
+    issue(t + kHStages);
+    frags(t + 1, an, bn);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][e] = mma_step(bf16_t{}, af[i], bf[e], acc[i][e]);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+      __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);     // two products
+    }
+  };
+  uint4 a0[8], b0[4], a1[8], b1[4];                // two fragment sets, used in turn
+  frags(0, a0, b0);
+  for (int t = 0; t < nk; t += 2) {
+    step(t, a0, b0, a1, b1);
+    if (t + 1 < nk) step(t + 1, a1, b1, a0, b0);
   }
   asm_wait_vmcnt<0>();                          // no copy still writes into the ring
   // epilogue: lane holds rows 4 g16 + k of each row tile, column c16 of each column tile

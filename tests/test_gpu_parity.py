@@ -1359,6 +1359,8 @@ PROJ_CASES = {
     "tiles_and_122_rows": (250, 1024, 4, 128, 5, None),
     "tiles_256_128_and_16_rows": (400, 1024, 4, 128, 7, None),
     "tiles_256_d64": (300, 512, 8, 64, 11, None),
+    "tiles_256_fewest_slices": (256, 128, 2, 128, 3, None),     # as many slices as ring stages
+    "tiles_256_12_slices": (258, 384, 4, 64, 9, None),
     "one_row": (1, 128, 1, 64, 7, None),
     "h2o_all_rows_sampled": (8194, 4096, 32, 128, 0, 48),
 }
