@@ -218,6 +218,14 @@ __global__ __launch_bounds__(kAttThreads) void cache_attention_f32_kernel(AttArg
 //            (two products, ~15 bits of weight); a lane holds 4 dimensions of its own row,
 //            so the rescale of a row is local to the lane.
 // The evicted-mass variant (MASS) stops after the sums.
+//   FULL: float32 weights, as three truncated bf16 parts that hold all 24 bits (three
+// products), and attend_row for every row whose sum or output is not finite: the products
+// take the V rows of whole subtiles, hidden ones times 0, in parts of a weight and against a
+// reference that may lie 2^100 below the row's maximum, so an infinity, a NaN or a value near
+// the top of the range can come out as one that the weights times the visible rows are not.
+// d = 64, 34 rows, 8 sequences of 2050 rows, 32 heads, attention and mass: 39 us, error
+// against 64 bits 2.2e-7; with two parts 35 us and 9.7e-6, the workgroup-per-row kernel of the
+// fp32 caches on bf16 1290 us and 8.1e-7.  d = 128, 70 rows: 103, 83 and 3650 us.
 // What bounds it (MI355X, 34 rows x 32 heads x 8 sequences over 2050 rows each, 256
 // workgroups): every compute unit reads its own 1 MB of K and V, 92 bytes per ns with one row
 // tile (a quarter of that from HBM or the Infinity Cache, the rest its XCD's L2); with three
@@ -255,7 +263,79 @@ __device__ __forceinline__ int att_swz(int r) {
   return D == 128 ? (r & 7) : ((r >> 1) & 3);
 }
 
-template <int D, int RT, bool MASS>
+// One query row done by the whole workgroup as the fp32 kernel does it: a running maximum,
+// float32 weights, the n_vis rows it sees and no others.  For the few rows whose result the
+// matrix-core loop cannot vouch for; lds is free.
+template <int D, bool MASS>
+__device__ __forceinline__ void attend_row(const AttArgs& a, int64_t ri, const char* kc, const char* vc,
+                                           int n_vis, char* lds) {
+  constexpr int T = AttWave<D, 1, MASS>::kThreads, W = T / kWave;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  float* qs = reinterpret_cast<float*>(lds);                   // [D]
+  float* ps = qs + D;                                          // [T] weights of a chunk
+  float* red = ps + T;                                         // [2][W] maxima, sums
+  const uint16_t* q = reinterpret_cast<const uint16_t*>(a.q) + ri * D;
+  auto f32 = [](uint32_t bf16_bits) { return __uint_as_float(bf16_bits << 16); };
+  __syncthreads();                                             // lds is free for everyone
+  if (tid < D) qs[tid] = f32(q[tid]);
+  float m = -INFINITY, sum = 0.0f, o = 0.0f;                   // o: dimension tid, tid < D
+  __syncthreads();
+  for (int c0 = 0; c0 < n_vis; c0 += T) {
+    const bool valid = c0 + tid < n_vis;
+    float x = -INFINITY;
+    if (valid) {
+      const char* row = kc + (int64_t)(c0 + tid) * (D * 2);
+      float acc = 0.0f;
+      for (int e = 0; e < D; e += 8) {
+        const uint4 u = load16(row + e * 2);
+        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc = fmaf(f32(w[i]), qs[e + 2 * i], acc);
+          acc = fmaf(f32(w[i] >> 16), qs[e + 2 * i + 1], acc);
+        }
+      }
+      x = acc * a.scale_log2;
+    }
+    float mx = x;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    if (lane == 0) red[wv] = mx;
+    __syncthreads();
+    float nm = m;
+#pragma unroll
+    for (int w = 0; w < W; ++w) nm = fmaxf(nm, red[w]);
+    const float alpha = rescale(m, nm), p = valid ? fast_exp2(x - nm) : 0.0f;
+    m = nm;
+    ps[tid] = p;
+    float s = p;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) red[W + wv] = s;
+    __syncthreads();                                           // ps and the sums are complete
+    float cs = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) cs += red[W + w];
+    sum = sum * alpha + cs;
+    if (!MASS && tid < D) {
+      const uint16_t* v = reinterpret_cast<const uint16_t*>(vc) + (int64_t)c0 * D + tid;
+      const int n = min(T, n_vis - c0);
+      o *= alpha;
+#pragma unroll 8
+      for (int t = 0; t < n; ++t) o = fmaf(ps[t], f32(v[(int64_t)t * D]), o);
+    }
+    __syncthreads();                                           // ps and red are free
+  }
+  const float lse_r = n_vis > 0 ? (m + __log2f(sum)) * 0.6931471805599453f : -INFINITY;
+  if constexpr (MASS) {
+    if (tid == 0) a.rho[ri] = -expm1f(-fmaxf(a.lse_full[ri] - lse_r, 0.0f));
+  } else {
+    if (tid < D) a.out[ri * D + tid] = n_vis > 0 ? o / sum : 0.0f;
+    if (tid == 0) a.lse[ri] = lse_r;
+  }
+}
+
+template <int D, int RT, bool MASS, bool FULL>
 __global__ __launch_bounds__((AttWave<D, RT, MASS>::kThreads), (AttWave<D, RT, MASS>::kPerSimd))
 void cache_attention_wave_kernel(AttArgs a) {
   using AT = AttWave<D, RT, MASS>;
@@ -281,6 +361,7 @@ void cache_attention_wave_kernel(AttArgs a) {
   const char* vc = MASS ? nullptr : reinterpret_cast<const char*>(a.v) + row0 * AT::kRowBytes;
   __shared__ __attribute__((aligned(1024))) char lds[AT::kLdsBytes];
   __shared__ float mfin[W][RT * 16], sfin[W][RT * 16], mrow[RT * 16], irow[RT * 16];
+  __shared__ int again[FULL ? RT * 16 : 1];                    // rows left to attend_row
 
   if (n_vis_max == 0) {                                        // nothing visible: no loads
     for (int r = r0 + wv; r <= r_last; r += W) {
@@ -407,7 +488,7 @@ void cache_attention_wave_kernel(AttArgs a) {
     wait_lgkmcnt0();                                           // fragments in registers
     copy_k(t + AT::kBuf * W, s);
     const int j0 = t * AT::kSub;
-    uint4 ph[MASS ? 1 : RT], pl[MASS ? 1 : RT];
+    uint4 ph[MASS ? 1 : RT], pl[MASS ? 1 : RT], pr[FULL && !MASS ? RT : 1];
     if (t < nt) {                                              // wave-uniform
     const bool masked = j0 + AT::kSub > n_vis_min;             // some key may be hidden
 #pragma unroll
@@ -470,8 +551,9 @@ void cache_attention_wave_kernel(AttArgs a) {
       ssum[i] = ns;
       if constexpr (!MASS) {
         // P ~ hi + lo: hi = the upper half of each float (a bf16 truncation), lo = the
-        // remainder, also truncated; packed two weights per register
-        uint32_t hb[4], lb[4];
+        // remainder, also truncated; packed two weights per register.  FULL: the remainder of
+        // lo has at most 8 significant bits and is the third part
+        uint32_t hb[4], lb[4], rb[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const uint32_t u0 = __float_as_uint(pv[2 * q]), u1 = __float_as_uint(pv[2 * q + 1]);
@@ -479,9 +561,15 @@ void cache_attention_wave_kernel(AttArgs a) {
           const float l1 = pv[2 * q + 1] - __uint_as_float(u1 & 0xffff0000u);
           hb[q] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
           lb[q] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+          if constexpr (FULL) {
+            const float r0 = l0 - __uint_as_float(__float_as_uint(l0) & 0xffff0000u);
+            const float r1 = l1 - __uint_as_float(__float_as_uint(l1) & 0xffff0000u);
+            rb[q] = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0), 0x07060302u);
+          }
         }
         ph[i] = make_uint4(hb[0], hb[1], hb[2], hb[3]);
         pl[i] = make_uint4(lb[0], lb[1], lb[2], lb[3]);
+        if constexpr (FULL) pr[i] = make_uint4(rb[0], rb[1], rb[2], rb[3]);
       }
     }
     }
@@ -511,6 +599,7 @@ void cache_attention_wave_kernel(AttArgs a) {
           for (int i = 0; i < RT; ++i) {
             o[i][dt] = mma_step(bf16_t{}, vf[dt], ph[i], o[i][dt]);
             o[i][dt] = mma_step(bf16_t{}, vf[dt], pl[i], o[i][dt]);
+            if constexpr (FULL) o[i][dt] = mma_step(bf16_t{}, vf[dt], pr[i], o[i][dt]);
           }
       }
     }
@@ -543,6 +632,7 @@ void cache_attention_wave_kernel(AttArgs a) {
       if constexpr (MASS) a.rho[row_base + r0 + tid] = -expm1f(-fmaxf(full - lse_r, 0.0f));
       else a.lse[row_base + r0 + tid] = lse_r;
     }
+    if constexpr (FULL) again[tid] = r0 + tid <= r_last && !(sf > 0.0f && sf < INFINITY);
     if constexpr (!MASS) {
       mrow[tid] = mf;
       irow[tid] = sf > 0.0f ? 1.0f / sf : 0.0f;
@@ -578,10 +668,18 @@ void cache_attention_wave_kernel(AttArgs a) {
           sum.w += p.w;
         }
         const float inv = irow[i0 * 16 + row];
-        *reinterpret_cast<float4*>(a.out + (row_base + r0 + i0 * 16 + row) * D + 4 * u) =
-            make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv);
+        sum = make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv);
+        *reinterpret_cast<float4*>(a.out + (row_base + r0 + i0 * 16 + row) * D + 4 * u) = sum;
+        if constexpr (FULL) {                                  // NaN unless all four are finite
+          if (!((sum.x + sum.y + sum.z + sum.w) * 0.0f == 0.0f)) again[i0 * 16 + row] = 1;
+        }
       }
     }
+  }
+  if constexpr (FULL) {
+    __syncthreads();
+    for (int r = r0; r <= r_last; ++r)                         // uniform
+      if (again[r - r0]) attend_row<D, MASS>(a, row_base + r, kc, vc, visible(r), lds);
   }
 }
 
@@ -618,9 +716,9 @@ hipError_t launch_att_f32(const AttArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int D, int RT, bool MASS>
+template <int D, int RT, bool MASS, bool FULL>
 hipError_t launch_att_wave(const AttArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((cache_attention_wave_kernel<D, RT, MASS>),
+  hipLaunchKernelGGL((cache_attention_wave_kernel<D, RT, MASS, FULL>),
                      dim3(xcd_grid(a.batch * a.n_kv_heads * a.G * a.row_blocks)),
                      dim3((AttWave<D, RT, MASS>::kThreads)), 0, st, a);
   if constexpr (MASS)
@@ -630,20 +728,29 @@ hipError_t launch_att_wave(const AttArgs& a, hipStream_t st) {
 
 // Row blocks of at most three 16-row tiles (what a wavefront's registers hold next to the
 // outputs), as equal as they come: 4 tiles are two blocks of two.
-template <int D, bool MASS>
+template <int D, bool MASS, bool FULL>
 hipError_t launch_att_blocks(AttArgs a, hipStream_t st) {
   const int tiles = (a.n_q + 15) / 16;
   a.row_blocks = (tiles + 2) / 3;
   const int rt = (tiles + a.row_blocks - 1) / a.row_blocks;
-  if (rt == 1) return launch_att_wave<D, 1, MASS>(a, st);
-  if (rt == 2) return launch_att_wave<D, 2, MASS>(a, st);
-  return launch_att_wave<D, 3, MASS>(a, st);
+  if (rt == 1) return launch_att_wave<D, 1, MASS, FULL>(a, st);
+  if (rt == 2) return launch_att_wave<D, 2, MASS, FULL>(a, st);
+  return launch_att_wave<D, 3, MASS, FULL>(a, st);
+}
+
+// FULL weights (see the kernel) but for the calls that have always had weights of two parts:
+// the attention at d = 128 and at most 64 rows.  The evicted mass has no weights; beyond 64
+// rows it keeps attend_row for sums that are not finite.
+template <int D, bool MASS>
+hipError_t launch_att_rows(const AttArgs& a, hipStream_t st) {
+  if (a.n_q > 64 || (!MASS && D == 64)) return launch_att_blocks<D, MASS, true>(a, st);
+  return launch_att_blocks<D, MASS, false>(a, st);
 }
 
 template <bool MASS>
 hipError_t launch_att_typed(const dge_geom_t& g, const AttArgs& a, hipStream_t st) {
   if (g.dtype == DGE_BF16)
-    return g.head_dim == 128 ? launch_att_blocks<128, MASS>(a, st) : launch_att_blocks<64, MASS>(a, st);
+    return g.head_dim == 128 ? launch_att_rows<128, MASS>(a, st) : launch_att_rows<64, MASS>(a, st);
   return g.head_dim == 128 ? launch_att_f32<128, MASS>(a, st) : launch_att_f32<64, MASS>(a, st);
 }
 

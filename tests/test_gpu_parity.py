@@ -893,6 +893,71 @@ def test_cache_attention_row_blocks_vs_oracle(d, hq, hkv, n_q, tail, kept):
             assert np.abs(l_match.cpu().numpy() - want).max() <= 2e-4
 
 
+def _att_inputs(d, hq, hkv, n_q, tail, kept, seed, v_scale=1.0):
+    rng = np.random.default_rng(seed)
+    B, n_sel = len(kept), max(kept)
+    g = dge.Geometry(hq, hkv, d, tail, 0, [n_sel + tail] * B, device=DEV)
+    bits = lambda *s, a=1.0: di.f32_to_bf16_bits((a * rng.standard_normal(s)).astype(np.float32))  # noqa: E731
+    q, k, v = bits(hq, B * n_q, d), bits(B, hkv, n_sel + tail, d), bits(B, hkv, n_sel + tail, d, a=v_scale)
+    nk = torch.tensor(list(kept) + [0] * 4, dtype=torch.int32, device=DEV)[:max(B, 4)]
+    return g, n_sel, nk, q, k, v
+
+
+# head dim, query rows: every bf16 call whose weights are float32 (head dim 64, more than 64 rows)
+FULL_WEIGHT_CASES = [(64, 1), (64, 16), (64, 34), (64, 70), (128, 65), (128, 97)]
+
+
+@pytest.mark.parametrize("d,n_q", FULL_WEIGHT_CASES)
+def test_cache_attention_float32_weights(d, n_q):
+    """Outputs carry the error of float32 weights and sums, about 2e-7 in the 2-norm; weights of
+    two bf16 parts have lost 2^-17 of each on average, 9e-6 of the output.  The bound lies
+    between: logits of normal rows are off by up to 2^-20, and so are the weights."""
+    kept = (700, 333)
+    g, n_sel, nk, qb, kb, vb = _att_inputs(d, 8, 2, n_q, n_q, kept, 900 + n_q)
+    _log(f"float32 weights d={d} n_q={n_q}")
+    f64 = [di.bf16_bits_to_f32(b).astype(np.float64) for b in (qb, kb, vb)]
+    for from_end in (n_q, 0):
+        out, _ = dge.cache_attention(g, to_dev(qb, "bf16"), n_q, from_end, to_dev(kb, "bf16"),
+                                     to_dev(vb, "bf16"), n_sel, n_q, nk)
+        torch.cuda.synchronize()
+        want, _ = oracle.cache_attention(*f64, kept, n_q, from_end, 8, 2)
+        err = np.linalg.norm(out.cpu().numpy() - want) / np.linalg.norm(want)
+        _log(f"  from_end={from_end}: error {err:.2e}")
+        assert err <= 2.0 ** -20
+
+
+@pytest.mark.parametrize("d,n_q", FULL_WEIGHT_CASES)
+def test_cache_attention_hidden_infinities_and_large_values(d, n_q):
+    """Rows attend what they see and nothing else: infinities and NaNs of V in a tail row (and
+    past a sequence's rows) reach only the query rows that see them, and values of V near the
+    top of the range times weights whose logits grow along the keys do not overflow."""
+    kept = (600, 288)
+    g, n_sel, nk, qb, kb, vb = _att_inputs(d, 4, 2, n_q, n_q, kept, 950 + n_q, v_scale=1e30)
+    _log(f"hidden infinities, large values d={d} n_q={n_q}")
+    q, k, v = (di.bf16_bits_to_f32(b) for b in (qb, kb, vb))
+    q = 0.1 * q + 4.0
+    k = 0.1 * k + (8.8 * np.sqrt(128 / d) * np.arange(k.shape[2]) / k.shape[2])[None, None, :, None]
+    for b, n in enumerate(kept):                 # the last query row alone sees the last tail row
+        v[b, :, n + n_q - 1, :3] = (np.inf, -np.inf, np.nan)
+        v[b, :, n + n_q:] = np.nan               # rows of no sequence
+    bits = [di.f32_to_bf16_bits(x.astype(np.float32)) for x in (q, k, v)]
+    f64 = [di.bf16_bits_to_f32(x).astype(np.float64) for x in bits]
+    qd, kd, vd = (to_dev(x, "bf16") for x in bits)
+    out, lse = dge.cache_attention(g, qd, n_q, n_q, kd, vd, n_sel, n_q, nk)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        want, want_l = oracle.cache_attention(*f64, kept, n_q, n_q, 4, 2)
+    got, got_l = out.cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64)
+    # logits of up to a few hundred carry float32 errors of 1e-6 of their size
+    assert (np.abs(got_l - want_l) <= 1e-4 + 1e-6 * np.abs(want_l)).all()
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.isposinf(got), np.isposinf(want))
+    assert np.array_equal(np.isneginf(got), np.isneginf(want))
+    fin = np.isfinite(want)
+    assert fin[:, :n_q - 1].all() and not fin[:, n_q - 1].all()
+    assert (np.abs(got[fin] - want[fin]) <= 1e30 * 1e-3 + 1e-3 * np.abs(want[fin])).all()
+
+
 MASS_CASES = {
     "c2_two_seqs": (di.small_variant("c2", [900, 1400]), None),
     "c1_f32_d64": (di.WORKLOADS["c1"], None),
