@@ -958,6 +958,39 @@ def test_cache_attention_hidden_infinities_and_large_values(d, n_q):
     assert (np.abs(got[fin] - want[fin]) <= 1e30 * 1e-3 + 1e-3 * np.abs(want[fin])).all()
 
 
+@pytest.mark.parametrize("kind", ["ramp", "step"])
+@pytest.mark.parametrize("d,n_q", [(64, 3), (64, 34), (128, 3), (128, 34), (128, 70)])
+def test_cache_attention_moving_references(d, n_q, kind):
+    """Logits that grow by hundreds of log2 units along the keys, over several rounds of the
+    eight wavefronts' 32-key subtiles: a row's reference moves again after its sums and outputs
+    are nonzero, and the wavefronts end with references far apart.  "ramp": linearly, so every
+    subtile moves it; "step": once, after the first 320 keys (a subtile for some wavefronts, two
+    for the others)."""
+    kept = (1500, 620)
+    g, n_sel, nk, qb, kb, vb = _att_inputs(d, 4, 2, n_q, n_q, kept, 990 + n_q)
+    _log(f"moving references d={d} n_q={n_q} {kind}")
+    q, k, v = (di.bf16_bits_to_f32(b) for b in (qb, kb, vb))
+    j = np.arange(k.shape[2])
+    r = 8.8 * j / k.shape[2] if kind == "ramp" else np.where(j < 320, 0.0, 1.9)
+    q = 0.1 * q + 4.0
+    k = 0.1 * k + (np.sqrt(128 / d) * r)[None, None, :, None]
+    bits = [di.f32_to_bf16_bits(x.astype(np.float32)) for x in (q, k, v)]
+    f64 = [di.bf16_bits_to_f32(x).astype(np.float64) for x in bits]
+    qd, kd, vd = (to_dev(x, "bf16") for x in bits)
+    out, lse = dge.cache_attention(g, qd, n_q, n_q, kd, vd, n_sel, n_q, nk)
+    want, want_l = oracle.cache_attention(*f64, kept, n_q, n_q, 4, 2)
+    lost = np.random.default_rng(5).random(want_l.shape) * 0.9
+    full = torch.from_numpy((want_l - np.log1p(-lost)).astype(np.float32)).to(DEV)
+    rho = dge.evicted_mass(g, qd, n_q, n_q, kd, n_sel, n_q, nk, full)[0]
+    torch.cuda.synchronize()
+    # logits of a few hundred carry float32 errors of 1e-6 of their size: so do the
+    # log-partitions, and weights and masses by as much
+    tol = 1e-4 + 1e-6 * np.abs(want_l)
+    assert (np.abs(lse.cpu().numpy() - want_l) <= tol).all()
+    assert (np.abs(rho.cpu().numpy() - lost) <= 2 * tol).all()
+    assert (np.abs(out.cpu().numpy() - want) <= 1e-3 * (1 + np.abs(want))).all()
+
+
 MASS_CASES = {
     "c2_two_seqs": (di.small_variant("c2", [900, 1400]), None),
     "c1_f32_d64": (di.WORKLOADS["c1"], None),
