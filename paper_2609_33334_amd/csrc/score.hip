@@ -1301,11 +1301,16 @@ ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
   // A launch of few rounds of workgroups (two per compute unit) leaves much of the chip idle
   // in a partial last round, so up to two rounds the walk is the one with the least rounds x
   // (tiles + kWalkStart), among those of at least kMinRoundWalk tiles (shorter ones are the
-  // business of the rule above); kWalkStart is what a workgroup's start costs in tiles.  Draft
-  // rows alone (fewer than four row tiles) start cheaply and gain nothing.
+  // business of the rule above) and at most kMaxRoundWalk: a walk is one serial float32 sum per
+  // lane, which should not grow with the sequence (131072 keys as one walk).  Error of the row
+  // log-sum-exp against 64 bits, rms and largest: walks of 52 tiles 5.2e-7 and 1.5e-6, of 129
+  // 5.0e-7 and 1.7e-6 (16384 tokens), of 64 tiles 6.6e-7 and 1.9e-6, of 257 6.0e-7 and 1.7e-6
+  // (65536 tokens); of 1025 the largest grows, 2.3e-6 against 1.9e-6.  kWalkStart is what a
+  // workgroup's start costs in tiles.  Draft rows alone (fewer than four row tiles) start
+  // cheaply and gain nothing.
   // 34 rows, 32 layers: 16384 tokens, 5 chunks (2.5 rounds) 449, 4 (two rounds) 443, 3 (1.5)
   // 452, 2 (one round) 433 us; 3000 tokens, one chunk (half a round) 91, two (one round) 86 us.
-  constexpr int64_t kRoundUnits = 512, kWalkStart = 4, kMinRoundWalk = 24;
+  constexpr int64_t kRoundUnits = 512, kWalkStart = 4, kMinRoundWalk = 24, kMaxRoundWalk = 256;
   auto cost = [&](int64_t walk, int64_t* rounds) {
     int64_t units = 0;
     for (int b = 0; b < g.batch; ++b)
@@ -1314,7 +1319,8 @@ ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
     return *rounds * (walk + kWalkStart);
   };
   int64_t rounds = 0, best = cost(iters, &rounds);
-  for (int64_t chunks = 1; p.n_tiles >= 4 && (seq_tiles + chunks - 1) / chunks >= kMinRoundWalk; ++chunks) {
+  for (int64_t chunks = (seq_tiles + kMaxRoundWalk - 1) / kMaxRoundWalk;
+       p.n_tiles >= 4 && (seq_tiles + chunks - 1) / chunks >= kMinRoundWalk; ++chunks) {
     const int64_t walk = (seq_tiles + chunks - 1) / chunks, c = cost(walk, &rounds);
     // more chunks than the rule above has only while their partials stay small (4 MiB), so
     // that a call which fits the fixed scratch keeps fitting it
