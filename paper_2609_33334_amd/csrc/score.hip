@@ -1305,27 +1305,37 @@ ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
   // lane, which should not grow with the sequence (131072 keys as one walk).  Error of the row
   // log-sum-exp against 64 bits, rms and largest: walks of 52 tiles 5.2e-7 and 1.5e-6, of 129
   // 5.0e-7 and 1.7e-6 (16384 tokens), of 64 tiles 6.6e-7 and 1.9e-6, of 257 6.0e-7 and 1.7e-6
-  // (65536 tokens); of 1025 the largest grows, 2.3e-6 against 1.9e-6.  kWalkStart is what a
+  // (65536 tokens); with 1025 the largest grew from 1.9e-6 to 2.3e-6.  kWalkStart is what a
   // workgroup's start costs in tiles.  Draft rows alone (fewer than four row tiles) start
   // cheaply and gain nothing.
   // 34 rows, 32 layers: 16384 tokens, 5 chunks (2.5 rounds) 449, 4 (two rounds) 443, 3 (1.5)
   // 452, 2 (one round) 433 us; 3000 tokens, one chunk (half a round) 91, two (one round) 86 us.
-  constexpr int64_t kRoundUnits = 512, kWalkStart = 4, kMinRoundWalk = 24, kMaxRoundWalk = 256;
-  auto cost = [&](int64_t walk, int64_t* rounds) {
+  constexpr int64_t kRoundUnits = 512, kWalkStart = 4, kMinRoundWalk = 24, kMaxRoundWalk = 192;
+  // Walks longer than the rule above has only where they gain: bf16 rows of d = 128 (or as
+  // many bytes), of which two workgroups share a compute unit (d = 64: more), and one round of
+  // at least four fifths.  Measured against that rule, times as fast: 1280 -> 512 workgroups
+  // (the 16384 tokens above) and 1152 -> 432 1.05, 864 -> 432 1.04, 1368 -> 456 (186 tiles)
+  // 1.01, but 448 of 239 tiles 0.97, two rounds (1224 -> 816, 1792 -> 896) 0.98, less of a
+  // round (1224 -> 408, 528 -> 264) 0.95; d = 64: 704 -> 352 0.84, 1248 -> 416 0.87, 1672 ->
+  // 456 0.96.
+  auto units_of = [&](int64_t walk) {
     int64_t units = 0;
     for (int b = 0; b < g.batch; ++b)
       units += ((g.kv_offsets_host[b + 1] - g.kv_offsets_host[b] + KT - 1) / KT + walk - 1) / walk;
-    *rounds = (units * g.n_kv_heads + kRoundUnits - 1) / kRoundUnits;
-    return *rounds * (walk + kWalkStart);
+    return units * g.n_kv_heads;
   };
-  int64_t rounds = 0, best = cost(iters, &rounds);
+  const int64_t row_bytes = (int64_t)g.head_dim * (g.dtype == DGE_BF16 ? 2 : 4);
+  const int base = iters;
+  int64_t best = (units_of(base) + kRoundUnits - 1) / kRoundUnits * (base + kWalkStart);
   for (int64_t chunks = (seq_tiles + kMaxRoundWalk - 1) / kMaxRoundWalk;
        p.n_tiles >= 4 && (seq_tiles + chunks - 1) / chunks >= kMinRoundWalk; ++chunks) {
-    const int64_t walk = (seq_tiles + chunks - 1) / chunks, c = cost(walk, &rounds);
+    const int64_t walk = (seq_tiles + chunks - 1) / chunks, units = units_of(walk);
+    const int64_t rounds = (units + kRoundUnits - 1) / kRoundUnits, c = rounds * (walk + kWalkStart);
+    if (rounds > 2) break;
+    if (walk > base && (row_bytes < 256 || rounds > 1 || 5 * units < 4 * kRoundUnits)) continue;
     // more chunks than the rule above has only while their partials stay small (4 MiB), so
     // that a call which fits the fixed scratch keeps fitting it
-    const bool room = walk >= iters || chunks * g.n_kv_heads * g.batch * p.M_pad * 4 <= (4 << 20);
-    if (rounds > 2) break;
+    const bool room = walk >= base || chunks * g.n_kv_heads * g.batch * p.M_pad * 4 <= (4 << 20);
     if (c < best && room) { best = c; iters = (int)walk; }
   }
   p.tiles_per_wave = iters;
@@ -1361,7 +1371,6 @@ ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
   // 4.7 -> 3.7 ms; 16 rows, 268 MB 106 either way, 1.07 GB 396 -> 342 us.  Buffers of 32, 64
   // and 128 MB for the 1.07 GB took 375, 297 and 290 us (each head range ends in a partial
   // round of workgroups), one range 275.
-  const int64_t row_bytes = (int64_t)g.head_dim * (g.dtype == DGE_BF16 ? 2 : 4);
   const int64_t head_bytes = p.M * logit_row_floats(g) * (int64_t)sizeof(float);
   if (p.M > 0 && p.n_tiles == 1 && 16 * p.M <= row_bytes && head_bytes <= kLogitBytes &&
       g.n_kv_heads * total_rows(g) * row_bytes >= kLogitMinK) {

@@ -146,13 +146,13 @@ def test_score_noalloc_validation(L):
 
 @pytest.mark.parametrize("hkv,n", [(512, 131072), (256, 131072), (512, 17000), (64, 1 << 20)])
 def test_score_walks_are_bounded(L, hkv, n):
-    """A scoring workgroup walks at most 256 tiles of 64 keys whatever the sequence's length
+    """A scoring workgroup walks at most 192 tiles of 64 keys whatever the sequence's length
     (its float32 sums are serial): the partials hold at least that many chunks per head."""
     G = _G(lens=(n,), hq=4 * hkv, hkv=hkv, w=34, k=0)
     size = ctypes.c_size_t(0)
     assert L.dge_workspace_size(G.p, 0, ctypes.byref(size)) == 0
     rows = 144                                            # 4 * 34 padded to 16
-    chunks = -(-(-(-n // 64)) // 256)
+    chunks = -(-(-(-n // 64)) // 192)
     assert size.value >= hkv * rows * 4 * (chunks + 1)    # partials and merged normalisers
 
 
