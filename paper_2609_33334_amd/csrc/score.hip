@@ -1350,12 +1350,20 @@ ScorePlan plan_score(const dge_geom_t& g, int rows_mode) {
   // sequences, row log-sum-exp given: 212 us by 55 tiles, 179 by 12, 183 by 24; 4 layers of
   // four sequences of 8K to 15K tokens 178 -> 156, 32 layers of three of 4K to 8K 493 -> 471
   // us); 140K tiles take the same time either way, and at 384K long walks are 2% faster.
+  // Not where the longer walks fill one round of two workgroups per compute unit and the short
+  // ones give the busiest unit at least 8/7 of that work (its workgroups times walk and start):
+  // 504 workgroups of 26 tiles 32.1, 560 of 23 37.4 us; 512 of 25 34, 576 of 22 41; 512 of 37
+  // 62, 896 of 21 70; 512 of 64 43, 1408 of 24 46.  With more than a round the short ones are
+  // mostly the faster at any ratio: 736 of 64 181, 2208 of 22 160; 720 of 57 214, 1640 of 24
+  // 187; but 1792 of 61 391, 4928 of 22 431.
   constexpr int64_t kColsumLongTiles = 128 * 1024;
   constexpr int kColsumWalk = 24;
   int citers = balanced((int)((tiles_total + 511) / 512));
   if (tiles_total < kColsumLongTiles && citers > kColsumWalk) {
     const int64_t chunks = (seq_tiles + kColsumWalk - 1) / kColsumWalk;
-    citers = (int)((seq_tiles + chunks - 1) / chunks);
+    const int64_t walk = (seq_tiles + chunks - 1) / chunks;
+    auto busiest = [&](int64_t w) { return (units_of(w) + 255) / 256 * (w + kWalkStart); };
+    if (units_of(citers) > kRoundUnits || 8 * busiest(citers) > 7 * busiest(walk)) citers = (int)walk;
   }
   p.c_tiles = citers;
   p.c_chunk_keys = KT * citers;
