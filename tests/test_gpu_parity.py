@@ -359,6 +359,37 @@ def test_score_stacked_layers_splits(nl, lens, supply_lse):
     check_scores(raw[0].cpu().numpy(), want, f"{nl} layers of {lens}")
 
 
+@pytest.mark.parametrize("supply_lse", [False, True])
+def test_score_steps_passed_and_derived_agree(supply_lse):
+    """Sixteen ragged sequences, whose keys per chunk come with the arguments, against the same
+    sequences in a batch of seventeen, where the kernel derives them: the key split is the
+    same, so the scores are the same bits; the oracle checks the last sequence's."""
+    lens = (700, 64, 65, 640, 34, 129, 383, 500, 257, 320, 100, 451, 611, 192, 35, 699)
+    _log(f"score steps, supply_lse={supply_lse}")
+    wl = di.small_variant("c2", [n - 2 for n in lens + (34,)])
+    x = di.make_layer(wl, with_v=False)
+    nr, T = wl.n_rows, sum(lens)
+    lse = oracle.scoring_row_lse(x.q, x.k, wl.kv_offsets, wl.n_q_heads, wl.n_kv_heads, wl.window,
+                                 wl.k_draft).astype(np.float32)
+    q, k, lse = to_dev(x.q_bits, "bf16"), to_dev(x.k_bits, "bf16"), torch.from_numpy(lse).to(DEV)
+    got = []
+    for n in (16, 17):
+        g = dge.Geometry(wl.n_q_heads, wl.n_kv_heads, wl.head_dim, wl.window, wl.k_draft,
+                         wl.cached_lens[:n], device=DEV)
+        assert g.total_rows * wl.n_kv_heads // 64 // 256 == 2          # walks of 3 tiles in both
+        qn, kn = q[:, :n * nr].contiguous(), k[:, :g.total_rows].contiguous()
+        if supply_lse:
+            raw = dge.score_lse(g, dge.ROWS_WINDOW_DRAFT, qn, kn, lse[:, :n * nr].contiguous())
+        else:
+            raw = dge.score(g, dge.ROWS_WINDOW_DRAFT, qn, kn)
+        torch.cuda.synchronize()
+        got.append(raw[:, :T].contiguous())
+    assert torch.equal(got[0].view(torch.int32), got[1].view(torch.int32))
+    want = oracle.window_scores(x.q, x.k, wl.kv_offsets, wl.n_q_heads, wl.n_kv_heads, wl.window,
+                                wl.k_draft)[:, :T]
+    check_scores(got[0].cpu().numpy(), want, "sixteen sequences")
+
+
 @pytest.mark.parametrize("case", ["c2", "c2_ragged", "c1"])
 def test_score_lse_single_pass(case):
     wl = {"c2": di.WORKLOADS["c2"], "c2_ragged": SCORE_CASES["c2_ragged"], "c1": di.WORKLOADS["c1"]}[case]
