@@ -55,7 +55,7 @@ typedef enum {
   DGE_OK = 0,
   DGE_ERR_INVALID = 1,      /* argument violates the documented contract */
   DGE_ERR_UNSUPPORTED = 2,  /* valid request this build does not implement (e.g. head_dim) */
-  DGE_ERR_WORKSPACE = 3,    /* workspace pointer NULL or smaller than dge_workspace_size */
+  DGE_ERR_WORKSPACE = 3,    /* workspace pointer NULL or too small for the call */
   DGE_ERR_HIP = 4           /* a HIP launch or runtime call failed */
 } dge_status_t;
 
@@ -96,15 +96,24 @@ int dge_abi_version(void);
 const char *dge_status_string(int status);
 
 /* Bytes of device workspace the given operation needs for this geometry.
- * DGE_OP_SCORE: per-row softmax partials of dge_score (the largest of the three row modes),
- *               and for launches of few scoring rows over a large K (e.g. draft rows over 32
- *               layers) up to 256 MiB for their logits; a smaller workspace that holds the
- *               partials is accepted and gives the same scores with a second pass over K.
+ * DGE_OP_SCORE: what serves dge_score with any of the three row modes; a caller that uses one
+ *               of them asks dge_score_workspace_size, which can be up to 256 MiB less.
  * DGE_OP_SELECT: radix keys of dge_select_topb.
  * DGE_OP_H2O: partial column sums of dge_h2o_colsum, plus the per-row log-sum-exp
  *             for calls where the caller supplies none.
  * Writes *bytes (host pointer).  Errors: DGE_ERR_INVALID for a bad geometry. */
 dge_status_t dge_workspace_size(const dge_geom_t *geom, int32_t op, size_t *bytes);
+
+/* Bytes of device workspace for dge_score and dge_score_with_lse with one row mode.
+ *   bytes : what the call makes use of: the rows' softmax partials and, for launches of few
+ *           scoring rows over a large K (e.g. draft rows over 32 layers), up to 256 MiB for
+ *           their logits.
+ *   least : the partials alone, the smallest workspace those calls accept; without room for
+ *           the logits they give the same scores with a second pass over K.
+ * Host pointers.  Errors: DGE_ERR_INVALID for a bad geometry, rows outside dge_rows_t or a
+ * NULL pointer. */
+dge_status_t dge_score_workspace_size(const dge_geom_t *geom, int32_t rows, size_t *bytes,
+                                      size_t *least);
 
 /* Step 1 of the eviction (Alg. 1 step B; App. "Diagnostic details"; App. "Complexity and overheads"):
  *   raw[h][j] = (1/G) sum_{g in group h} sum_{scoring rows r} softmax_j(q_{g,r} . k_j / sqrt(d))
@@ -116,7 +125,7 @@ dge_status_t dge_workspace_size(const dge_geom_t *geom, int32_t op, size_t *byte
  *         head hq / G.
  *   k   : keys, layout above.
  *   raw : [H_kv][T] float32 output.
- *   ws  : workspace of at least dge_workspace_size(geom, DGE_OP_SCORE) bytes.
+ *   ws  : workspace of dge_score_workspace_size bytes for these rows (at least its `least`).
  * Errors: DGE_ERR_INVALID if a sequence has fewer than w + k rows or n_rows == 0;
  * DGE_ERR_UNSUPPORTED for head_dim outside {64, 128}. */
 dge_status_t dge_score(const dge_geom_t *geom, int32_t rows, const void *q, const void *k,
@@ -140,8 +149,8 @@ dge_status_t dge_score_with_lse(const dge_geom_t *geom, int32_t rows, const void
  * kernels and results as dge_score (bit-identical), with the softmax partials kept in a
  * fixed scratch array that the library holds in every GPU's memory until the process
  * ends.  No allocation of any kind is made by this call.
- *   Limit: the call needs dge_workspace_size(geom, DGE_OP_SCORE)-style scratch for its
- *   rows mode of at most DGE_NOALLOC_SCRATCH_BYTES (16 MiB: e.g. 64 layers x 8 KV heads x
+ *   Limit: the partials of its rows (the `least` of dge_score_workspace_size) take at most
+ *   DGE_NOALLOC_SCRATCH_BYTES (16 MiB: e.g. 64 layers x 8 KV heads x
  *   8 sequences of up to 32K rows, 34 scoring rows, G = 4); larger geometries return
  *   DGE_ERR_WORKSPACE before anything is launched.
  *   Every call on one GPU shares that GPU's scratch, and calls keep no state in it between

@@ -8,7 +8,7 @@ Every step of the path runs in the library's HIP kernels.
 
 Names follow the C ABI: ``score`` (dge_score), ``select_topb``,
 ``select_streaming``, ``compact``, ``h2o_colsum``, ``pyramid_budgets``,
-``workspace_size``; ``evict_layer`` chains score -> select_topb -> compact.
+``workspace_size``, ``score_workspace_size``; ``evict_layer`` chains score -> select_topb -> compact.
 """
 from __future__ import annotations
 
@@ -26,7 +26,7 @@ __all__ = ["Geometry", "score", "score_noalloc", "score_with_lse", "score_lse", 
            "select_compact_layers", "select_streaming", "compact", "compact_inplace",
            "cache_attention",
            "rope", "project_rope", "project_rope_workspace", "retained_runs", "h2o_colsum",
-           "pyramid_budgets", "workspace_size", "evict_layer", "DGEError", "ROWS_WINDOW_DRAFT",
+           "pyramid_budgets", "workspace_size", "score_workspace_size", "evict_layer", "DGEError", "ROWS_WINDOW_DRAFT",
            "ROWS_DRAFT", "ROWS_WINDOW", "n_scoring_rows"]
 
 
@@ -143,6 +143,25 @@ def _workspace(geom: Geometry, op: int, ws):
     return ws
 
 
+def score_workspace_size(geom: Geometry, rows: int) -> tuple:
+    """dge_score_workspace_size: (bytes score makes use of with these rows, least it accepts)."""
+    n, least = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    _lib.check(_lib.lib().dge_score_workspace_size(ctypes.byref(geom.c), rows, ctypes.byref(n),
+                                                   ctypes.byref(least)), "dge_score_workspace_size")
+    return int(n.value), int(least.value)
+
+
+def _score_workspace(geom: Geometry, rows: int, ws):
+    torch = _torch()
+    if ws is None:
+        n, least = score_workspace_size(geom, rows)
+        try:
+            ws = torch.empty(n, dtype=torch.uint8, device=geom.device)
+        except torch.OutOfMemoryError:      # no room for kept logits: the same scores without
+            ws = torch.empty(least, dtype=torch.uint8, device=geom.device)
+    return ws
+
+
 def score(geom: Geometry, rows: int, q, k, raw=None, ws=None, stream=None):
     """dge_score: raw[h][j] for every cached key.  Returns raw [H_kv][T] float32."""
     torch = _torch()
@@ -153,7 +172,7 @@ def score(geom: Geometry, rows: int, q, k, raw=None, ws=None, stream=None):
     if raw is None:
         raw = torch.empty(geom.n_kv_heads, geom.total_rows, dtype=torch.float32, device=geom.device)
     _need(raw, "raw", _f32(), geom.n_kv_heads * geom.total_rows)
-    ws = _workspace(geom, OP_SCORE, ws)
+    ws = _score_workspace(geom, rows, ws)
     _lib.check(_lib.lib().dge_score(ctypes.byref(geom.c), rows, _ptr(q), _ptr(k), _ptr(raw),
                                     _ptr(ws), ws.numel(), _stream(stream)), "dge_score")
     return raw
@@ -175,7 +194,7 @@ def score_with_lse(geom: Geometry, rows: int, q, k, raw=None, row_lse=None, ws=N
                               device=geom.device)
     _need(raw, "raw", _f32(), geom.n_kv_heads * geom.total_rows)
     _need(row_lse, "row_lse", _f32(), geom.n_q_heads * geom.batch * nr)
-    ws = _workspace(geom, OP_SCORE, ws)
+    ws = _score_workspace(geom, rows, ws)
     _lib.check(_lib.lib().dge_score_with_lse(ctypes.byref(geom.c), rows, _ptr(q), _ptr(k),
                                              _ptr(raw), _ptr(row_lse), _ptr(ws), ws.numel(),
                                              _stream(stream)), "dge_score_with_lse")

@@ -19,7 +19,8 @@ ABI_VERSION = 1
 NOALLOC_SCRATCH_BYTES = 16 << 20   # DGE_NOALLOC_SCRATCH_BYTES
 
 # every entry point declared in include/dge.h
-EXPORTS = ("dge_abi_version", "dge_status_string", "dge_workspace_size", "dge_score",
+EXPORTS = ("dge_abi_version", "dge_status_string", "dge_workspace_size",
+           "dge_score_workspace_size", "dge_score",
            "dge_score_noalloc", "dge_score_with_lse", "dge_score_lse", "dge_evicted_mass",
            "dge_select_topb", "dge_select_compact", "dge_select_compact_layers",
            "dge_select_streaming", "dge_compact", "dge_compact_inplace",
@@ -68,6 +69,8 @@ def lib() -> ctypes.CDLL:
     L.dge_status_string.argtypes = [c_int]
     L.dge_workspace_size.restype = c_int
     L.dge_workspace_size.argtypes = [GP, c_int32, POINTER(c_size_t)]
+    L.dge_score_workspace_size.restype = c_int
+    L.dge_score_workspace_size.argtypes = [GP, c_int32, POINTER(c_size_t), POINTER(c_size_t)]
     L.dge_score.restype = c_int
     L.dge_score.argtypes = [GP, c_int32, c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]
     L.dge_score_noalloc.restype = c_int

@@ -134,6 +134,18 @@ dge_status_t dge_workspace_size(const dge_geom_t* geom, int32_t op, size_t* byte
   }
 }
 
+dge_status_t dge_score_workspace_size(const dge_geom_t* geom, int32_t rows, size_t* bytes,
+                                      size_t* least) {
+  if (bytes == nullptr || least == nullptr) return DGE_ERR_INVALID;
+  if (rows < DGE_ROWS_WINDOW_DRAFT || rows > DGE_ROWS_WINDOW) return DGE_ERR_INVALID;
+  const dge_status_t st = check_geom(geom);
+  if (st != DGE_OK) return st;
+  const ScorePlan p = dge::plan_score(*geom, rows);
+  *least = dge::score_workspace_bytes(*geom, p);
+  *bytes = *least + dge::score_logit_bytes(*geom, p);
+  return DGE_OK;
+}
+
 dge_status_t dge_score(const dge_geom_t* geom, int32_t rows, const void* q, const void* k,
                        float* raw, void* ws, size_t ws_bytes, hipStream_t stream) {
   dge_status_t st = check_score(geom, rows, q, k, raw);

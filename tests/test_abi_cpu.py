@@ -206,6 +206,32 @@ def test_workspace_size(L):
     assert L.dge_workspace_size(g.p, 0, None) == _lib.DGE_ERR_INVALID
 
 
+def test_score_workspace_size(L):
+    """By row mode: only few rows over a large K count logits; dge_workspace_size covers all."""
+    def sizes(G, rows):
+        n, least = ctypes.c_size_t(0), ctypes.c_size_t(0)
+        assert L.dge_score_workspace_size(G.p, rows, ctypes.byref(n), ctypes.byref(least)) == 0
+        return n.value, least.value
+    layers = _G(lens=(16384,), hq=1024, hkv=256, w=32, k=2)         # 32 layers of one prompt
+    logits = 4 * 1024 * 2 * 16384
+    for rows in (_lib.ROWS_WINDOW_DRAFT, _lib.ROWS_WINDOW):
+        n, least = sizes(layers, rows)
+        assert n == least < 16 << 20
+    n, least = sizes(layers, _lib.ROWS_DRAFT)
+    assert least < 16 << 20 and logits <= n - least < logits + (1 << 20)
+    op = ctypes.c_size_t(0)
+    assert L.dge_workspace_size(layers.p, 0, ctypes.byref(op)) == 0 and op.value == n
+    n, least = sizes(_G(), _lib.ROWS_DRAFT)                          # a small K
+    assert n == least
+    g, c = _G(), ctypes.c_size_t(0)
+    f = L.dge_score_workspace_size
+    assert f(g.p, 3, ctypes.byref(c), ctypes.byref(c)) == _lib.DGE_ERR_INVALID
+    assert f(g.p, -1, ctypes.byref(c), ctypes.byref(c)) == _lib.DGE_ERR_INVALID
+    assert f(g.p, 0, None, ctypes.byref(c)) == _lib.DGE_ERR_INVALID
+    assert f(g.p, 0, ctypes.byref(c), None) == _lib.DGE_ERR_INVALID
+    assert f(_G(d=96).p, 0, ctypes.byref(c), ctypes.byref(c)) == _lib.DGE_ERR_UNSUPPORTED
+
+
 def test_select_validation(L):
     g = _G()
     def sel(pool=7, n_tail=10, n_select=20, idx=FAKE, nk=FAKE, ws=FAKE, nbytes=1 << 40):

@@ -42,6 +42,35 @@ def test_score_refuses_wrong_dtype_size_and_device():
         dge.score(g, dge.ROWS_WINDOW_DRAFT, q, k, raw=raw)
 
 
+@pytest.mark.parametrize("full", [False, True])
+def test_score_allocates_for_its_rows(monkeypatch, full):
+    """Without a workspace, score takes what its own row mode uses (scores by window rows never
+    keep logits, however large K is), and the partials alone where the device is full."""
+    g = dge.Geometry(1024, 256, 128, 32, 2, [16384], dtype=dge.DGE_BF16, device="cpu")
+    got = []
+    empty = torch.empty
+
+    def alloc(*shape, **kw):
+        if kw.get("dtype") is torch.uint8:
+            got.append(shape[0])
+            if full and shape[0] > 64 << 20:
+                raise torch.OutOfMemoryError("full")
+            return empty(16, **kw)
+        return empty(*shape, **kw)
+
+    monkeypatch.setattr(torch, "empty", alloc)
+    monkeypatch.setattr(dge, "_need", lambda *a, **kw: None)
+    for call in (dge.score, dge.score_with_lse):
+        for rows in (dge.ROWS_WINDOW_DRAFT, dge.ROWS_WINDOW, dge.ROWS_DRAFT):
+            got.clear()
+            with pytest.raises(ValueError, match="needs a GPU tensor"):
+                call(g, rows, empty(4), empty(4), raw=empty(4))
+            if rows != dge.ROWS_DRAFT:
+                assert len(got) == 1 and got[0] < 16 << 20
+            else:
+                assert got[0] > 128 << 20 and got[1:] == ([dge.score_workspace_size(g, rows)[1]] if full else [])
+
+
 def test_select_and_compact_refuse_wrong_index_types():
     g = dge.Geometry(4, 2, 64, 2, 1, [40, 50], dtype=dge.DGE_F32, device="cpu")
     scores = torch.zeros(2, 90, dtype=torch.float32)
