@@ -53,6 +53,8 @@ struct H2oArgs {
   int64_t total_rows;
   int n_q_heads, n_kv_heads, G, batch;
   int n_rblk;           // lse: 128-row blocks of the longest sequence
+  int log_stripes;      // lse: 8 / gcd(8, H_kv) stripes of a KV head's blocks, its log2 ...
+  int stripe_blk;       // ... of so many blocks each
   float scale_log2;
   float inv_G;
 };
@@ -88,8 +90,12 @@ __device__ __forceinline__ uint4 lds_frag(const char* lds, int r, int s, int g16
 
 // ------------------------------------------------------------------------------------
 // Row log-sum-exp: one (query head, 128-row block, sequence) per workgroup, whose walk over
-// the keys is as long as its block is late: units run from the last blocks to the first
-// within each KV head, so the short ones fill the end of the launch.  Splitting the keys,
+// the keys is as long as its block is late: units run from the last blocks to the first, so
+// the short ones fill the end of the launch.  Each XCD takes a contiguous eighth of the units,
+// which is whole KV heads or, if 8 does not divide them, whole stripes of a head: every
+// 2nd, 4th or 8th of its blocks, so that no XCD holds the late half of a head (8192 rows, 4
+// query heads per KV head, both passes, unstriped and striped: 1 KV head 185 and 171 us, 2 304
+// and 233, 4 427 and 351, 6 542 and 513, 12 973 and 902).  Splitting the keys,
 // not the heads, over the wavefronts keeps all four busy for any group size (a wavefront
 // per head of the group left three of four idle at G = 1), and 128 rows per 16-key subtile
 // read a quarter of LDS per product.  The next subtile's fragments are read and its buffer
@@ -98,17 +104,23 @@ __device__ __forceinline__ uint4 lds_frag(const char* lds, int r, int s, int g16
 // heads on 8 KV heads and 4004 rows 150 -> 110 us, at 8 on 8 and 1.5-1.8K rows 65 -> 48 us.
 // ------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256, 2) void h2o_lse_kernel(H2oArgs a) {
-  const int units = a.n_rblk * a.n_q_heads * a.batch;
-  const int unit = xcd_unit(units);
+  const int units = (a.stripe_blk << a.log_stripes) * a.n_q_heads * a.batch;
+  int unit = xcd_unit(units);               // ((h * stripes + stripe) * stripe_blk + i, b, g)
   if (unit >= units) return;
-  const int per_kv = a.n_rblk * a.batch * a.G;
-  const int h = unit / per_kv, in_h = unit % per_kv;
-  const int rblk = a.n_rblk - 1 - in_h / (a.batch * a.G);     // the longest walks first
-  const int b = in_h / a.G % a.batch, hq = h * a.G + in_h % a.G;
+  const int g = unit % a.G;
+  unit /= a.G;
+  const int b = unit % a.batch;
+  unit /= a.batch;
+  const int i = unit % a.stripe_blk;
+  unit /= a.stripe_blk;
+  const int last = (1 << a.log_stripes) - 1, stripe = unit & last, h = unit >> a.log_stripes;
+  const int hq = h * a.G + g;
+  // the longest walks of the stripe first; stripes deal the blocks out to and fro
+  const int rblk = a.n_rblk - 1 - (i << a.log_stripes) - ((i & 1) ? last - stripe : stripe);
   const int64_t s0 = a.offs[b];
   const int N = (int)(a.offs[b + 1] - s0);
   const int r0 = rblk * RBL;
-  if (r0 >= N) return;                      // a shorter sequence of a ragged batch
+  if (r0 < 0 || r0 >= N) return;            // past the stripe, a shorter sequence of a ragged batch
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);    // wave-uniform
   const int g16 = lane >> 4, c16 = lane & 15;
@@ -428,8 +440,11 @@ hipError_t launch_h2o(const dge_geom_t& g, const void* q_all, const void* k, con
   if (lse == nullptr) {
     a.lse_out = reinterpret_cast<float*>(ws);
     a.n_rblk = (int)((nmax + RBL - 1) / RBL);
-    hipLaunchKernelGGL(h2o_lse_kernel, dim3(xcd_grid(a.n_rblk * g.n_q_heads * g.batch)),
-                       dim3(256), 0, st, a);
+    while ((g.n_kv_heads << a.log_stripes) % kXcds != 0) ++a.log_stripes;
+    a.stripe_blk = (a.n_rblk + (1 << a.log_stripes) - 1) >> a.log_stripes;
+    hipLaunchKernelGGL(h2o_lse_kernel,
+                       dim3(xcd_grid((a.stripe_blk << a.log_stripes) * g.n_q_heads * g.batch)), dim3(256),
+                       0, st, a);
     a.lse = a.lse_out;
   } else {
     a.lse = lse;

@@ -701,6 +701,21 @@ def test_h2o_group_sizes_and_tile_edges(lens, n_q_heads, supply_lse):
     check_scores(col.cpu().numpy(), want, "h2o_edges")
 
 
+@pytest.mark.parametrize("n_kv_heads", [1, 2, 3, 4, 12, 16])
+def test_h2o_kv_head_counts(n_kv_heads):
+    """KV head counts that 8 XCDs do and do not divide: the row log-sum-exp pass deals a head's
+    blocks out in 8 / gcd(8, heads) stripes, of which some end past the first block."""
+    lens = (1400, 129)
+    _log(f"h2o {n_kv_heads} KV heads, lens={lens}")
+    wl = dataclasses.replace(di.small_variant("c5", [n - 2 for n in lens]), n_q_heads=2 * n_kv_heads,
+                             n_kv_heads=n_kv_heads)
+    x = di.make_layer(wl, with_v=False)
+    col = dge.h2o_colsum(geom_of(wl), to_dev(x.q_all_bits, "bf16"), to_dev(x.k_bits, "bf16"))
+    torch.cuda.synchronize()
+    want = oracle.h2o_colsum(x.q_all, x.k, wl.kv_offsets, wl.n_q_heads, wl.n_kv_heads)
+    check_scores(col.cpu().numpy(), want, f"h2o {n_kv_heads} KV heads")
+
+
 @pytest.mark.parametrize("kind", ["ramp", "step"])
 def test_wide_logit_range_scores_and_h2o_vs_oracle(kind):
     wl, x = _wide_logit_layer(kind, (700, 130))
