@@ -14,8 +14,8 @@
 //
 // colsum: a workgroup owns a 128-key block and a 512-row segment of one KV head.  For every
 //   query head of the group, 64-row blocks of Q and their log-sum-exp stream through a
-//   three-stage LDS ring (global->LDS copies); a wavefront takes 64 of the keys, held in
-//   registers, and 32 rows of every block.  With A = query rows, a lane holds 4 rows of
+//   LDS ring (global->LDS copies); a wavefront takes 64 of the keys, held in registers, and
+//   32 rows of every block, or 32 keys and 64 rows.  With A = query rows, a lane holds 4 rows of
 //   one key: P = 2^(x - lse) is summed in the lane and crosses lanes once, at the end of
 //   the segment.  A small reduction adds the segments' partial sums in a fixed order.
 //
@@ -225,15 +225,18 @@ __global__ __launch_bounds__(256, 2) void h2o_lse_kernel(H2oArgs a) {
 // cost the same, and not sequences (three sequences of 2.1K to 4.0K rows: 232 -> 165 us,
 // the XCDs that held the longest one having had 1.5 times the mean work).  Each unit
 // writes the partial column sums of its 128 keys to part[s][h][j]; h2o_reduce_kernel adds
-// the segments in a fixed order.  A wavefront's 64 keys x 32 rows read half of LDS per
-// product that 32 keys x 64 rows did (8192 rows, lse given: 298 -> 288 us); three
-// workgroups per compute unit (139 registers, 52 KB).
+// the segments in a fixed order.  From three query heads per KV head on, a wavefront takes 64
+// keys x 32 rows, which read half of LDS per product that 32 keys x 64 rows do, and the ring
+// has three stages: three workgroups per compute unit (138 registers, 52 KB).  At one or two
+// heads a unit is too short for that (8 or 16 blocks) and spends its time on its start: 32
+// keys x 64 rows load each key once instead of twice, and two stages leave room for four
+// workgroups (35 KB).  8 KV heads, lse given, 32 x 64 against 64 x 32: G = 1, 1100 rows x 2
+// 15.6 and 16.9 us, 7500 rows 76.5 and 81.4; G = 2, 2300 x 2 38.2 and 40.7, 7500 136.5 and
+// 136.9; G = 4, 7500 258 and 251.
 // ------------------------------------------------------------------------------------
 constexpr int SEG = 512;
-constexpr int kColStages = 3;
 constexpr int kColCopies = RB * RowBytes / (256 * 16) + 1;     // per thread: 4 of Q, 1 of lse
 constexpr int kColStageBytes = RB * RowBytes + 4 * RB * 4;     // Q block; lse once per wavefront
-constexpr int NKT = 4;           // 16-key tiles of K per wavefront
 
 // 4 bytes per lane from global memory straight into LDS (see dma16_sbase).
 __device__ __forceinline__ void dma4_sbase(const void* sbase, uint32_t voff, uint32_t lds_wave_base) {
@@ -249,14 +252,14 @@ __device__ __forceinline__ void dma4_sbase(const void* sbase, uint32_t voff, uin
       : "memory");
 }
 
-// 32 query rows (two row tiles at LDS rows rw0) against the wavefront's 64 keys.
+// The wavefront's query rows of a block (8 / NKT row tiles from LDS row rw0) against its keys.
 // MASK: rows at or past row_end, and keys past a row, add nothing.
-template <bool MASK>
+template <bool MASK, int NKT>
 __device__ __forceinline__ void colsum_rows(const char* qt, const float* lt, int rw0, int r0, int row_end,
                                             int j0, int c16, int g16, const uint4 (&kf)[NKT][NS],
                                             float scale, float (&col)[NKT]) {
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
+  for (int rt = 0; rt < 8 / NKT; ++rt) {
     const int rl = rw0 + rt * 16;
     uint4 qf[NS];
 #pragma unroll
@@ -285,7 +288,8 @@ __device__ __forceinline__ void colsum_rows(const char* qt, const float* lt, int
   }
 }
 
-__global__ __launch_bounds__(256, 3) void h2o_colsum_kernel(H2oArgs a, float* part, int nkb_max,
+template <int NKT, int S>
+__global__ __launch_bounds__(256, S == 2 ? 4 : 3) void h2o_colsum_kernel(H2oArgs a, float* part, int nkb_max,
                                                          int nseg_max) {
   const int units = nkb_max * nseg_max * a.n_kv_heads * a.batch;
   const int unit = xcd_unit(units);
@@ -301,10 +305,11 @@ __global__ __launch_bounds__(256, 3) void h2o_colsum_kernel(H2oArgs a, float* pa
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
   const int g16 = lane >> 4, c16 = lane & 15;
-  const int j0 = k0 + (wv & 1) * 64;           // this wavefront's 64 keys
-  const int rw0 = (wv >> 1) * 32;              // and its 32 rows of every block
-  __shared__ __attribute__((aligned(16))) char ring[kColStages][kColStageBytes];
-  __shared__ float half_sum[2][64];
+  constexpr int KW = 16 * NKT, RW = 64 * 32 / KW, NW = KB / KW;   // keys, rows of a wavefront
+  const int j0 = k0 + wv % NW * KW;            // this wavefront's keys
+  const int rw0 = wv / NW * RW;                // and its rows of every block
+  __shared__ __attribute__((aligned(16))) char ring[S][kColStageBytes];
+  __shared__ float half_sum[NW][KW];
 
   const int rlo = max(seg_lo, k0 / RB * RB);   // first 64-row block with rows >= k0
   const int per = (seg_hi - rlo + RB - 1) / RB;
@@ -347,8 +352,8 @@ __global__ __launch_bounds__(256, 3) void h2o_colsum_kernel(H2oArgs a, float* pa
     }
   }
 #pragma unroll
-  for (int t = 0; t < kColStages - 1; ++t) issue(t);
-  asm_wait_vmcnt<(kColStages - 2) * kColCopies>();     // block 0 (and the keys) landed
+  for (int t = 0; t < S - 1; ++t) issue(t);
+  asm_wait_vmcnt<(S - 2) * kColCopies>();     // block 0 (and the keys) landed
   uint4 kf[NKT][NS];
 #pragma unroll
   for (int t = 0; t < NKT; ++t)
@@ -362,19 +367,19 @@ __global__ __launch_bounds__(256, 3) void h2o_colsum_kernel(H2oArgs a, float* pa
   for (int t = 0; t < NKT; ++t) col[t] = 0.0f;
   int r0 = rlo, slot = 0;
   for (int it = 0; it < nblk; ++it) {
-    asm_wait_vmcnt<(kColStages - 2) * kColCopies>();   // block it landed (own copies)
+    asm_wait_vmcnt<(S - 2) * kColCopies>();   // block it landed (own copies)
     lds_barrier();                                     // ... everyone's; the last slot is free
-    issue(slot == 0 ? kColStages - 1 : slot - 1);
+    issue(slot == 0 ? S - 1 : slot - 1);
     const char* qt = ring[slot];
     const float* lt = reinterpret_cast<const float*>(qt + RB * RowBytes) + wv * RB;
     // masking only in the (rare) edge blocks: the common body has no branch per logit
-    if (r0 + rw0 >= j0 + 63 && r0 + RB <= seg_hi)
-      colsum_rows<false>(qt, lt, rw0, r0, seg_hi, j0, c16, g16, kf, a.scale_log2, col);
-    else if (r0 + rw0 + 31 >= j0)
-      colsum_rows<true>(qt, lt, rw0, r0, seg_hi, j0, c16, g16, kf, a.scale_log2, col);
+    if (r0 + rw0 >= j0 + KW - 1 && r0 + RB <= seg_hi)
+      colsum_rows<false, NKT>(qt, lt, rw0, r0, seg_hi, j0, c16, g16, kf, a.scale_log2, col);
+    else if (r0 + rw0 + RW - 1 >= j0)
+      colsum_rows<true, NKT>(qt, lt, rw0, r0, seg_hi, j0, c16, g16, kf, a.scale_log2, col);
     r0 += RB;
     if (r0 >= seg_hi) r0 = rlo;
-    slot = slot + 1 == kColStages ? 0 : slot + 1;
+    slot = slot + 1 == S ? 0 : slot + 1;
   }
   asm_wait_vmcnt<0>();                         // no copy still writes into the ring
 #pragma unroll
@@ -382,17 +387,17 @@ __global__ __launch_bounds__(256, 3) void h2o_colsum_kernel(H2oArgs a, float* pa
     col[t] += shfl_xor_f<16>(col[t]);
     col[t] += shfl_xor_f<32>(col[t]);
   }
-  if (wv >= 2 && g16 == 0) {
+  if (wv >= NW && g16 == 0) {
 #pragma unroll
-    for (int t = 0; t < NKT; ++t) half_sum[wv & 1][16 * t + c16] = col[t];
+    for (int t = 0; t < NKT; ++t) half_sum[wv % NW][16 * t + c16] = col[t];
   }
-  __syncthreads();
-  if (wv < 2 && g16 == 0) {
+  if constexpr (NW < 4) __syncthreads();
+  if (wv < NW && g16 == 0) {
     float* out = part + ((int64_t)seg * a.n_kv_heads + h) * a.total_rows + s0;
 #pragma unroll
     for (int t = 0; t < NKT; ++t) {
       const int j = 16 * t + c16;
-      if (j0 + j < N) out[j0 + j] = col[t] + half_sum[wv][j];
+      if (j0 + j < N) out[j0 + j] = NW < 4 ? col[t] + half_sum[wv][j] : col[t];
     }
   }
 }
@@ -453,7 +458,8 @@ hipError_t launch_h2o(const dge_geom_t& g, const void* q_all, const void* k, con
   const int nseg = (int)((nmax + SEG - 1) / SEG);
   const size_t lse_bytes = ((size_t)g.n_q_heads * (size_t)a.total_rows * sizeof(float) + 255) / 256 * 256;
   float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + lse_bytes);
-  hipLaunchKernelGGL(h2o_colsum_kernel, dim3(xcd_grid(nkb * nseg * g.n_kv_heads * g.batch)),
+  const auto kernel = a.G <= 2 ? h2o_colsum_kernel<2, 2> : h2o_colsum_kernel<4, 3>;
+  hipLaunchKernelGGL(kernel, dim3(xcd_grid(nkb * nseg * g.n_kv_heads * g.batch)),
                      dim3(256), 0, st, a, part, nkb, nseg);
   hipLaunchKernelGGL(h2o_reduce_kernel, dim3((unsigned)((nmax + 255) / 256), g.n_kv_heads, g.batch),
                      dim3(256), 0, st, a, part);
