@@ -4,7 +4,7 @@
 //   softmax over keys j <= p_r (causal), fp32 after the bf16/fp32 product.
 //
 // A column sum needs every scoring row's global normaliser first, so one layer runs
-// as three launches over the same split of the keys into chunks:
+// as three launches, the two passes over K each with its own split of the keys into chunks:
 //   1. stats : each workgroup streams its chunk of K and keeps, per query row, the
 //              running (max, sum of 2^(x - max)) of its logits (log2 domain), stored
 //              as one log2-sum-exp per row and chunk;
@@ -336,19 +336,18 @@ constexpr int score_waves() {
 }
 template <typename T, int D, int FT, int RT>
 constexpr int stats_waves() { return score_waves<T, D, FT, RT>(); }
-// The colsum pass at Llama-3-8B-like row counts (bf16, d = 128, at most two own and one
-// shared tile per wavefront) also fits three wavefronts per SIMD (<= 168 registers) with a
-// 3-stage ring; the stats pass at three spills.  Three are as fast as two on the shortest
-// walks (one layer of 4096 and 16000 tokens, 34 rows: 20.6 against 20.9 and 29.2 against
-// 29.7 us for the three launches) and faster on longer ones (4 layers, four sequences of 8K
-// to 15K tokens: 174 -> 162 us; 12 layers, two of 6K to 9K: 172 -> 161 us).  With fewer than
-// four row tiles (draft rows) a walk is bound by its copies and two wavefronts with the
-// 4-stage ring are faster (8 layers of 8000 tokens, 32 rows: 47.0 against 49.7 us) up to
-// kColsumThreeWaveUnits workgroups.
-constexpr int kColsumThreeWaveUnits = 4096;
+// The colsum pass at Llama-3-8B-like row counts (bf16, d = 128, one or two own tiles per
+// wavefront and at most one shared) also fits three wavefronts per SIMD (<= 168 registers)
+// with a 3-stage ring; the stats pass at three spills.  Three are as fast as two on the
+// shortest walks (one layer of 4096 and 16000 tokens, 34 rows: 20.6 against 20.9 and 29.2
+// against 29.7 us for the three launches) and faster on longer ones (4 layers, four sequences
+// of 8K to 15K tokens: 174 -> 162 us; 12 layers, two of 6K to 9K: 172 -> 161 us).  One shared
+// tile alone (at most 16 query rows) is bound by its copies and stays at two with the 4-stage
+// ring, log-sum-exp given, two against three: 2816 workgroups 198 and 203 us, 5632 385 and 395,
+// 512 and fewer the same.
 template <typename T, int D, int FT, int RT>
 constexpr int colsum_waves() {
-  return std::is_same<T, bf16_t>::value && D == 128 && FT <= 2 && RT <= 1
+  return std::is_same<T, bf16_t>::value && D == 128 && FT >= 1 && FT <= 2 && RT <= 1
              ? 3 : score_waves<T, D, FT, RT>();
 }
 
@@ -1229,14 +1228,8 @@ hipError_t launch_typed(const ScoreArgs& a, const dge_geom_t& g, hipStream_t st)
       return hipGetLastError();
     }
   }
-  constexpr int W2 = score_waves<T, D, FT, RT>(), W3 = colsum_waves<T, D, FT, RT>();
-  if constexpr (FT == 0 && W3 != W2) {
-    if (cunits < kColsumThreeWaveUnits) {
-      hipLaunchKernelGGL((score_colsum_kernel<T, D, FT, RT, W2>), gridc, dim3(kThreads), 0, st, ac);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((score_colsum_kernel<T, D, FT, RT, W3>), gridc, dim3(kThreads), 0, st, ac);
+  constexpr int W = colsum_waves<T, D, FT, RT>();
+  hipLaunchKernelGGL((score_colsum_kernel<T, D, FT, RT, W>), gridc, dim3(kThreads), 0, st, ac);
   return hipGetLastError();
 }
 
