@@ -419,8 +419,8 @@ dge_status_t dge_retained_runs(const dge_geom_t *geom, const int32_t *idx, const
  *   colsum : [H_kv][T] float32 output; each sequence's colsum sums to N_b.
  *   ws     : dge_workspace_size(geom, DGE_OP_H2O) bytes (per-segment partial column sums,
  *            and the row LSE when lse == NULL).
- * Only bfloat16 inputs with head_dim 128 are supported, and computing the LSE in the
- * library needs G <= 4 query heads per KV head (DGE_ERR_UNSUPPORTED otherwise). */
+ * Only bfloat16 inputs with head_dim 128 are supported, and the library computes the LSE for
+ * up to 4 query heads per KV head (DGE_ERR_UNSUPPORTED otherwise): larger groups supply it. */
 dge_status_t dge_h2o_colsum(const dge_geom_t *geom, const void *q_all, const void *k,
                             const float *lse, float *colsum, void *ws, size_t ws_bytes,
                             hipStream_t stream);

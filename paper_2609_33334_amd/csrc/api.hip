@@ -414,6 +414,8 @@ dge_status_t dge_h2o_colsum(const dge_geom_t* geom, const void* q_all, const voi
   if (!q_all || !k || !colsum || !aligned16(q_all) || !aligned16(k) || !aligned16(colsum) ||
       (lse && !aligned16(lse)))
     return DGE_ERR_INVALID;
+  // the contract's limit, not the kernels': the row pass takes a query head per workgroup at
+  // any group size, but has been validated up to 4
   if (lse == nullptr && geom->n_q_heads / geom->n_kv_heads > 4) return DGE_ERR_UNSUPPORTED;
   if (ws == nullptr || !aligned16(ws) || ws_bytes < dge::h2o_workspace_bytes(*geom))
     return DGE_ERR_WORKSPACE;
