@@ -109,9 +109,9 @@ dge_status_t dge_workspace_size(const dge_geom_t *geom, int32_t op, size_t *byte
  *           scoring rows over a large K (e.g. draft rows over 32 layers), up to 256 MiB for
  *           their logits.
  *   least : the partials alone, the smallest workspace those calls accept; without room for
- *           the logits they give the same scores with a second pass over K.
+ *           the logits they give the same scores with a second pass over K.  May be NULL.
  * Host pointers.  Errors: DGE_ERR_INVALID for a bad geometry, rows outside dge_rows_t or a
- * NULL pointer. */
+ * NULL bytes pointer. */
 dge_status_t dge_score_workspace_size(const dge_geom_t *geom, int32_t rows, size_t *bytes,
                                       size_t *least);
 

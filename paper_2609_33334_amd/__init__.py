@@ -154,11 +154,14 @@ def score_workspace_size(geom: Geometry, rows: int) -> tuple:
 def _score_workspace(geom: Geometry, rows: int, ws):
     torch = _torch()
     if ws is None:
-        n, least = score_workspace_size(geom, rows)
+        n = ctypes.c_size_t(0)
+        _lib.check(_lib.lib().dge_score_workspace_size(ctypes.byref(geom.c), rows, ctypes.byref(n),
+                                                       None), "dge_score_workspace_size")
         try:
-            ws = torch.empty(n, dtype=torch.uint8, device=geom.device)
+            ws = torch.empty(n.value, dtype=torch.uint8, device=geom.device)
         except torch.OutOfMemoryError:      # no room for kept logits: the same scores without
-            ws = torch.empty(least, dtype=torch.uint8, device=geom.device)
+            ws = torch.empty(score_workspace_size(geom, rows)[1], dtype=torch.uint8,
+                             device=geom.device)
     return ws
 
 

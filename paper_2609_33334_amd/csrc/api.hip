@@ -136,13 +136,14 @@ dge_status_t dge_workspace_size(const dge_geom_t* geom, int32_t op, size_t* byte
 
 dge_status_t dge_score_workspace_size(const dge_geom_t* geom, int32_t rows, size_t* bytes,
                                       size_t* least) {
-  if (bytes == nullptr || least == nullptr) return DGE_ERR_INVALID;
+  if (bytes == nullptr) return DGE_ERR_INVALID;
   if (rows < DGE_ROWS_WINDOW_DRAFT || rows > DGE_ROWS_WINDOW) return DGE_ERR_INVALID;
   const dge_status_t st = check_geom(geom);
   if (st != DGE_OK) return st;
   const ScorePlan p = dge::plan_score(*geom, rows);
-  *least = dge::score_workspace_bytes(*geom, p);
-  *bytes = *least + dge::score_logit_bytes(*geom, p);
+  const size_t partials = dge::score_workspace_bytes(*geom, p);
+  *bytes = partials + dge::score_logit_bytes(*geom, p);
+  if (least != nullptr) *least = partials;
   return DGE_OK;
 }
 

@@ -228,7 +228,7 @@ def test_score_workspace_size(L):
     assert f(g.p, 3, ctypes.byref(c), ctypes.byref(c)) == _lib.DGE_ERR_INVALID
     assert f(g.p, -1, ctypes.byref(c), ctypes.byref(c)) == _lib.DGE_ERR_INVALID
     assert f(g.p, 0, None, ctypes.byref(c)) == _lib.DGE_ERR_INVALID
-    assert f(g.p, 0, ctypes.byref(c), None) == _lib.DGE_ERR_INVALID
+    assert f(g.p, 0, ctypes.byref(c), None) == 0 and c.value == sizes(g, 0)[0]
     assert f(_G(d=96).p, 0, ctypes.byref(c), ctypes.byref(c)) == _lib.DGE_ERR_UNSUPPORTED
 
 
